@@ -191,7 +191,8 @@ __global__ __launch_bounds__(256) void cgemm_kernel(CgArgs a) {
                 }
         }
     }
-    // lane l holds rows 4(l/16) + r of column l % 16 of each 16 x 16 tile
+    // result register r of lane l holds column l % 16 of each 16 x 16 tile, row
+    // 4(l/16) + r (FP32) or 4r + l/16 (FP64)
     V *C = static_cast<V *>(a.C) + (int64_t)b * a.sC;
     for (int j = 0; j < 2; ++j) {
         const int col = n0 + wc + 16 * j + lr;
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(256) void cgemm_kernel(CgArgs a) {
         if (GEPI) gc = a.g0[col];
         for (int i = 0; i < TM; ++i)
             for (int r = 0; r < 4; ++r) {
-                const int row = m0 + wr + 16 * i + 4 * slot + r;
+                const int row = m0 + wr + 16 * i + (sizeof(T) == 4 ? 4 * slot + r : 4 * r + slot);
                 if (row >= a.M) continue;
                 double cr = (double)re[i][j][r], ci = (double)im[i][j][r];
                 if (GEPI) {

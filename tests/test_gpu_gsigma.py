@@ -77,6 +77,21 @@ def test_full_matrix_matches_oracle(w, n, spin, c128):
 
 
 @pytest.mark.parametrize("c128", [True, False], ids=["c128", "c64"])
+@pytest.mark.parametrize("nw,nwex", [(6, 4), (8, 3), (8, 6), (16, 6)], ids=["ng18", "ng20", "ng26", "ng42"])
+def test_window_with_a_partial_last_row_block(nw, nwex, c128):
+    """Ng is not a multiple of the matrix instruction's 16 rows."""
+    w = Workload("gsig-ragged", lx=2, ly=1, nw=nw, nwex=nwex, nq=1, beta=5.0, mu=0.1, h=0.2, t=1.0)
+    n = 19
+    print(f"\ncase ng={w.ng} n={n} c128={c128}", flush=True)
+    tau, site, M = expansion_configs(w, 41 + w.ng, 2, n)
+    got = run(w, 1, tau, site, M, c128)
+    Mo = oracle_inputs(M, c128)
+    for b in range(2):
+        want = ref.gsigma(w, 1, tau[b], site[b], Mo[b])
+        assert corr_err(got[b], want, g0_diag(w, 1)[:, None], np.eye(w.ng, dtype=bool)) <= tol_for(c128, n)
+
+
+@pytest.mark.parametrize("c128", [True, False], ids=["c128", "c64"])
 def test_no_vertices_gives_g0(c128):
     print(f"\ncase n=0 c128={c128}", flush=True)
     w = TILES
