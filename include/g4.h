@@ -123,7 +123,8 @@ enum {
 
 /* how measurements are applied */
 enum {
-    G4_MODE_PLAIN = 0,    /* one kernel pass over the slice per measurement */
+    G4_MODE_PLAIN = 0,    /* one kernel pass over the slice per measurement (g4_accumulate_into: the
+                             same operations in the same order, several measurements per pass) */
     G4_MODE_BATCHED = 1   /* up to max_batch measurements fused in one pass */
 };
 

@@ -183,11 +183,16 @@ struct GatherArgs {
                         // (G_up + G_dn), bit 2 up-up (G_up, G_up), bit 3 up-down (G_up, G_dn)
     Dims d;
     Tables t;
+    // Weights passed by value: the gather (or pack) uses sgn[] and stores the
+    // pass's weights at sign_out for the update kernel that follows, so a pass
+    // has no host-to-device copy of its own (a 2.7 us copy kernel and its gap).
+    double *sign_out = nullptr;      // null: the weights are read from `sign`
+    double sgn[kMaxPassBatch];
 };
 
 // Kernel launchers (g4_kernels.hip).  Gather `prec` 0 = FP64, 1 = FP32.
 // Update `kind` 0 = plain FP64 (one measurement per pass), 1 = batched FP64,
-// 2 = batched FP32.
+// 2 = batched FP32.  A gather with no slots only stores the weights.
 hipError_t launch_gather(int prec, const GatherArgs &a, hipStream_t s);
 // `variant` 0 = VALU kernel, 1 = MFMA direct term (kind 2, tile 16, nw % 64 == 0),
 // 2 = packed operands staged straight into LDS (kind 2, even tile).

@@ -22,9 +22,17 @@ template <> struct Cx<float> { using V = float2; };
 // Direct-term vectors: element (slot, b, p, K) at slot*dir_slot_stride +
 // b*dir_b_stride + p*n + K; slot 0 = magnetic (G_up - G_dn), slot 1 = charge
 // (G_up + G_dn), present when the slot bit is set.
+// weight of measurement b, and the store of all of them by one block
+__device__ __forceinline__ double weight(const GatherArgs &a, int b) { return a.sign_out ? a.sgn[b] : a.sign[b]; }
+__device__ __forceinline__ void store_weights(const GatherArgs &a, bool this_block) {
+    if (a.sign_out && this_block && (int)threadIdx.x < a.batch) a.sign_out[threadIdx.x] = a.sgn[threadIdx.x];
+}
+
 template <typename R>
 __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     using V = typename Cx<R>::V;
+    store_weights(a, blockIdx.x == 0);
+    if (!a.slots) return;
     const int n = a.d.n, nw = a.d.nw, nwg = a.d.nwg, nc = a.d.nc, planes = a.d.planes;
     const int64_t ng = a.d.ng;
     const int64_t total = (int64_t)a.batch * planes * n;
@@ -43,7 +51,7 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
         const V *gd = static_cast<const V *>(a.gd) + (int64_t)b * a.g_stride;
         const V au = gu[rKQ * ng + rK], ad = gd[rKQ * ng + rK];
         const V bu = gu[rK * ng + rKQ], bd = gd[rK * ng + rKQ];
-        const R s = (R)a.sign[b];
+        const R s = (R)weight(a, b);
         V *da = static_cast<V *>(a.dir_a);
         V *db = static_cast<V *>(a.dir_b);
         int64_t o = (int64_t)b * a.dir_b_stride + (int64_t)p * n + K;
@@ -84,6 +92,7 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
 __global__ __launch_bounds__(256) void pack_gather_kernel(PackArgs pa) {
     const GatherArgs &a = pa.g;
     const int64_t b = blockIdx.y;
+    store_weights(a, blockIdx.x == 0 && b == 0);
     const int ng = a.d.ng, nwg = a.d.nwg, nw = a.d.nw, nwex = a.d.nwex, nc = a.d.nc, n = a.d.n;
     // Blocks are dealt to the 8 XCDs in turn; each XCD takes a contiguous run of
     // rows, so the direct-vector elements that consecutive rows write into one
@@ -113,7 +122,7 @@ __global__ __launch_bounds__(256) void pack_gather_kernel(PackArgs pa) {
     for (int c = nc * pcb + threadIdx.x; c < pa.ldp; c += 256) d[c] = float4{0.f, 0.f, 0.f, 0.f};
     if (!a.slots) return;
     const int kr = R / nwg, rho = R - kr * nwg;
-    const float s = (float)a.sign[b];
+    const float s = (float)weight(a, (int)b);
     float2 *da = static_cast<float2 *>(a.dir_a) + b * a.dir_b_stride;
     float2 *db = static_cast<float2 *>(a.dir_b) + b * a.dir_b_stride;
     for (int e = threadIdx.x; e < 2 * nc * nwex; e += 256) {
@@ -385,7 +394,8 @@ G4_PDECL(1) G4_PDECL(2) G4_PDECL(4) G4_PDECL(8)
 #undef G4_PDECL
 
 hipError_t launch_gather(int prec, const GatherArgs &a, hipStream_t s) {
-    const int64_t total = (int64_t)a.batch * a.d.planes * a.d.n;
+    if (a.batch > kMaxPassBatch || (!a.slots && !a.sign_out)) return a.slots ? hipErrorInvalidValue : hipSuccess;
+    const int64_t total = a.slots ? (int64_t)a.batch * a.d.planes * a.d.n : 1;
     if (total == 0) return hipSuccess;
     const int g = grid_for(total, 256);
     if (prec == 0)
@@ -434,7 +444,7 @@ hipError_t launch_pack_gather(const PackArgs &a, hipStream_t s) {
     const int count = a.g.batch, ng = a.g.d.ng;
     if (count == 0) return hipSuccess;
     if (a.pcb < a.g.d.nwg || a.pcb % 8 || a.ldp < a.g.d.nc * a.pcb + 1 || a.pack_stride16 < (int64_t)ng * a.ldp ||
-        count > 65535)
+        count > kMaxPassBatch)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(pack_gather_kernel, dim3(8 * ((ng + 7) / 8), count), dim3(256), 0, s, a);
     return hipGetLastError();
