@@ -8,6 +8,7 @@
 #include <dlfcn.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -17,6 +18,8 @@
 #include <new>
 #include <sstream>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "g4_internal.hpp"
@@ -70,6 +73,8 @@ constexpr int kMaxNw = 256;      // one K1 row per lane group of a 256-thread bl
 constexpr int kMaxBatch = kMaxPassBatch;
 constexpr int kSignSlots = 8;
 constexpr uint64_t kScratchEntries = 4u << 20;   // readback/load staging, complex128
+constexpr int kReadbackLanes = 8;                // threads of a large readback, one pinned slot each
+constexpr uint64_t kLaneEntries = kScratchEntries / kReadbackLanes;   // 8 MiB per slot
 
 int acc_entry_bytes(int acc) { return acc == G4_ACC_C64 ? 8 : 16; }
 
@@ -474,6 +479,7 @@ struct g4_slice {
     bool sign_ev_used[kSignSlots] = {};
     int sign_next = 0;
     double *scratch = nullptr;
+    void *readback_host = nullptr;   // pinned, kReadbackLanes slots; allocated by the first large readback
     int *finite_dev = nullptr;       // G4_F_CHECK_FINITE: set by the check kernel
     int *finite_host = nullptr;      // pinned copy of it
     uint64_t measurements = 0;
@@ -564,6 +570,7 @@ void release(g4_slice *h) {
         if (p) (void)hipFree(p);
     if (h->sign_host) (void)hipHostFree(h->sign_host);
     if (h->finite_host) (void)hipHostFree(h->finite_host);
+    if (h->readback_host) (void)hipHostFree(h->readback_host);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
 }
@@ -921,6 +928,60 @@ int run_plain(g4_slice *h, const char *gu, const char *gd, const double *sign, i
     return G4_OK;
 }
 
+// A readback of several slots' worth of entries: kReadbackLanes threads take
+// slot-sized ranges in turn, each converting into its own part of the scratch,
+// copying that to its own pinned slot and from there to the caller's memory, so
+// that the device copies follow one another (57 GB/s) while the other threads
+// move what has arrived.  One thread through the runtime's staging of pageable
+// memory took 202 ms for the 2.15 GB of the 4x4 slice, this 46 ms (47 GB/s).
+// *ran = false (nothing done) where the pinned slots or the threads cannot be had.
+int readback_lanes(g4_slice *h, int c, uint64_t first, uint64_t count, double *out, bool *ran) {
+    *ran = false;
+    if (!h->readback_host) {
+        if (hipHostMalloc(&h->readback_host, kScratchEntries * 16, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            h->readback_host = nullptr;
+            return G4_OK;
+        }
+    }
+    std::atomic<uint64_t> next{0};
+    std::atomic<int> bad{(int)hipSuccess};
+    const uint64_t ranges = (count + kLaneEntries - 1) / kLaneEntries;
+    auto lane = [&](int i) {
+        double *dev = h->scratch + 2 * i * kLaneEntries;
+        double *host = static_cast<double *>(h->readback_host) + 2 * i * kLaneEntries;
+        hipEvent_t ev = nullptr;
+        hipError_t e = hipSetDevice(h->device);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        for (uint64_t r; e == hipSuccess && bad.load() == (int)hipSuccess && (r = next.fetch_add(1)) < ranges;) {
+            const uint64_t off = r * kLaneEntries, cnt = std::min(kLaneEntries, count - off);
+            e = launch_acc_to_c128(h->cfg.acc, h->acc[c], first + off, cnt, dev, h->P.d.nc, h->P.d.nw, h->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(host, dev, cnt * 16, hipMemcpyDeviceToHost, h->stream);
+            if (e == hipSuccess) e = hipEventRecord(ev, h->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(ev);
+            if (e == hipSuccess) std::memcpy(out + 2 * off, host, cnt * 16);
+        }
+        if (ev) (void)hipEventDestroy(ev);
+        if (e != hipSuccess) bad.store((int)e);
+    };
+    std::vector<std::thread> threads;
+    try {
+        threads.reserve(kReadbackLanes - 1);
+        for (int i = 1; i < kReadbackLanes; ++i) threads.emplace_back(lane, i);
+    } catch (const std::exception &) {
+        // fewer threads: the ones there, and this one, take every range
+    }
+    lane(0);
+    for (auto &t : threads) t.join();
+    *ran = true;
+    const hipError_t e = (hipError_t)bad.load();
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(h->stream);
+        return hip_fail(h, e, "readback");
+    }
+    return G4_OK;
+}
+
 }  // namespace
 
 namespace {
@@ -1269,6 +1330,11 @@ int g4_readback(g4_slice *h, uint32_t channel, uint64_t first, uint64_t count, d
     if (count && !out) return fail(G4_E_ARG, "out is NULL");
     G4_HIP(h, hipSetDevice(h->device));
     G4_HIP(h, hipStreamSynchronize(h->stream));
+    if (count >= kScratchEntries) {     // then the scratch holds all slots
+        bool ran = false;
+        if (rc = readback_lanes(h, c, first, count, out, &ran); rc) return rc;
+        if (ran) return fold_timings(h);
+    }
     const uint64_t chunk = h->P.scratch_bytes / 16;
     for (uint64_t off = 0; off < count; off += chunk) {
         const uint64_t cnt = std::min(chunk, count - off);
