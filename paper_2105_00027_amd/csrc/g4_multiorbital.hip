@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <cstdio>
+#include <type_traits>
 #include <vector>
 
 namespace g4 {
@@ -41,6 +42,10 @@ constexpr int kMoPlanes = 256;   // planes per launch
 // 2x2 cluster with 4 orbitals) in the last-level cache; 64 per launch took
 // 3.27 ms per 64 measurements there, 32 3.18 ms
 constexpr int kMoBatch = 32;
+// measurements per launch of mo_mfma_kernel, which sums kMoBatch at a time and
+// those sums in a second set of registers: one trip of the accumulator to memory
+// and back per 128 measurements
+constexpr int kMoLong = 128;
 
 struct MoArgs {
     const void *gu, *gd;
@@ -50,7 +55,7 @@ struct MoArgs {
     int64_t side;                // N nb^2
     int lx, ly, nw, nwg, nb, ngb, channel, batch, planes;
     int2 qm[kMoPlanes];          // (q, m) per plane of the launch
-    double sign[kMoBatch];
+    double sign[kMoLong];
 };
 
 template <typename R> struct MoCx;
@@ -308,6 +313,260 @@ __global__ __launch_bounds__(256) void mo_rows_kernel(MoArgs a) {
         }
 }
 
+// Four orbitals, FP32: the orbital labels of one (Q, K1, K2) make the exchange
+// (and PP) term a 16 x 16 outer product summed over measurements and spins,
+//   PH  [(b1, b4), (b3, b2)] += G_s(K1+Q b1, K2+Q b4) (-s_b G_s(K2 b3, K1 b2)),
+//   PP  [(b2, b4), (b3, b1)] += G_s(Q-K2 b4, Q-K1 b2) ( s_b G_{-s}(K2 b3, K1 b1)),
+// so it runs on v_mfma_f32_16x16x4f32, whose four k slots are four measurements
+// of one spin: four instructions (Re Re, Im Re, Im Im, Re Im) a spin.
+// Result register r of lane l is row 4(l/16) + r, column l % 16: the lane holds
+// (h = b1 or b2; b3, c = b2 or b1) of all four b4.  The PH direct term
+// a(b1, b2) b(b3, b4) is sixteen 4 x 4 outer products (b1, b3) and lands in the
+// same registers through v_mfma_f32_4x4x1_16b_f32, whose block l/4 is (b1, b3),
+// column l % 4 = b2 and register row b4.  Both run at the full FP32 matrix rate
+// (twice the vector one): 96 matrix cycles per 256 entries and measurement.
+// A wave takes TQ planes x 4 K2 of one K1 (8 accumulator registers a tile, and 8
+// for the sums of every 32 measurements): the column operand G(K2, K1) is loaded
+// once for its planes, the row operand once a tile, straight into the lanes that
+// multiply it; each is replaced by the next step's (four measurements, one spin)
+// as soon as it has been used, a whole step ahead.
+// The block's four waves are four neighbouring K1; the direct operands of its
+// 4 K1, 4 K2 and TQ planes are formed once in LDS, four measurements at a time.
+// The 2x2 cluster, Nw = 32, 16 planes, 256 measurements: 13.0 ms on the vector
+// units (eight launches, 30 TFLOP/s), here 7.0 ms (59 TFLOP/s; 2.7 ms at the rate
+// of a large FP32 product).  What is left is the operands' way from L2: runs of
+// four elements (32 bytes); with the row operand always in L1 5.1 ms.
+template <int TQ, bool PP>
+__global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    constexpr int NB = 4, TK = 4;
+    __shared__ int win1[4], win2[TK], pl1[4][TQ], pl2[TK][TQ];      // window indices of K and of K+Q (PP: Q-K)
+    __shared__ float wt[kMoLong];                                   // weights, zeros past the batch
+    __shared__ float2 Ash[4][64 * TQ], Bsh[4][64 * TQ];            // [measurement][K of four][plane][orbitals]
+    const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ngb = a.ngb;
+    const int n = (int)(a.side / (NB * NB));
+    // Each XCD takes a contiguous run of squares of 8 x 8 blocks (32 K1 x 32 K2,
+    // what its CUs hold at once), a square's plane groups one after another: the
+    // squares share rows and columns of G in its L2 (runs of all K1 at 8 K2 read
+    // 2.3 times the lines).
+    const int s1 = (n + 31) / 32, gq = (a.planes + TQ - 1) / TQ;
+    const int per = gridDim.x / 8;
+    const int wk = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    const int in = wk % 64, pb = (wk / 64) % gq * TQ, sq = wk / 64 / gq;
+    const int k1b = (sq % s1 * 8 + in % 8) * 4, k2b = (sq / s1 * 8 + in / 8) * 4;
+    if (k1b >= n || k2b >= n) return;                 // squares past the end
+    // past the end the last K, plane and measurement repeat: loaded, never used
+    if (tid < kMoLong) wt[tid] = tid < a.batch ? (float)a.sign[tid] : 0.f;
+    if (tid < 4 * (TQ + 1) * 2) {
+        const int side2 = tid >= 4 * (TQ + 1), e = tid - side2 * 4 * (TQ + 1), j = e / (TQ + 1), t = e % (TQ + 1);
+        const int nw = a.nw, nwg = a.nwg, lx = a.lx, ly = a.ly;
+        const int K = min((side2 ? k2b : k1b) + j, n - 1), k = K / nw, i = K % nw;
+        if (t == TQ) {
+            (side2 ? win2 : win1)[j] = k * nwg + i;
+        } else {
+            const int2 qm = a.qm[min(pb + t, a.planes - 1)];
+            const int kx = k % lx, ky = k / lx, qx = qm.x % lx, qy = qm.x / lx;
+            (side2 ? pl2 : pl1)[j][t] =
+                PP ? ((qx - kx + lx) % lx + lx * ((qy - ky + ly) % ly)) * nwg + qm.y + nw - 1 - i
+                   : ((kx + qx) % lx + lx * ((ky + qy) % ly)) * nwg + i + qm.y;
+        }
+    }
+    __syncthreads();
+    const int hi = (l >> 2) & 3, lo = l & 3;          // row operand (h, b4) and column operand (b3, c) of lane l % 16
+    const unsigned gs = (unsigned)(a.g_stride * 8);   // four matrices below 2^32 bytes (launch_mo)
+    // byte offsets from a step's first matrix: this lane's measurement, its element
+    unsigned xo[TK], yo[TK][TQ];
+#pragma unroll
+    for (int j = 0; j < TK; ++j) {
+        xo[j] = (unsigned)((win2[j] * NB + hi) * ngb + win1[w] * NB + lo) * 8;
+#pragma unroll
+        for (int t = 0; t < TQ; ++t)
+            yo[j][t] = (unsigned)(PP ? (pl2[j][t] * NB + lo) * ngb + pl1[w][t] * NB + hi
+                                     : (pl1[w][t] * NB + hi) * ngb + pl2[j][t] * NB + lo) * 8;
+    }
+    const int par = l >> 4;
+    f4 re[TK][TQ], im[TK][TQ], rs[TK][TQ], is[TK][TQ];   // sums of up to 32 measurements, and of those sums
+#pragma unroll
+    for (int j = 0; j < TK; ++j)
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) re[j][t] = im[j][t] = rs[j][t] = is[j][t] = f4{0.f, 0.f, 0.f, 0.f};
+
+    // direct operands: a thread forms one (K of four, plane, orbital pair) of each side; threads past them repeat
+    const int sid = TQ == 4 ? tid : tid % (64 * TQ);
+    const int sk = sid / (TQ * 16), st = (sid / 16) % TQ, se = sid & 15;
+    unsigned ao = 0, bo = 0;
+    if (!PP) {
+        ao = (unsigned)((pl1[sk][st] * NB + (se >> 2)) * ngb + win1[sk] * NB + (se & 3)) * 8;
+        bo = (unsigned)((win2[sk] * NB + (se >> 2)) * ngb + pl2[sk][st] * NB + (se & 3)) * 8;
+    }
+    const float sg = a.channel == CH_MAG ? -1.f : 1.f;
+    const char *const gu = static_cast<const char *>(a.gu), *const gd = static_cast<const char *>(a.gd);
+    auto at = [](const char *b, unsigned o) __attribute__((always_inline)) { return *reinterpret_cast<const float2 *>(b + o); };
+    float2 x[2][TK], y[2][TK][TQ], du[4], dd[4];      // [spin]
+    // a step's operands: uniform base, this lane's measurement (the last one past the batch)
+    auto lane_off = [&](int b) { return (unsigned)min(par, a.batch - 1 - b) * gs; };
+    // this thread's element of one side's direct operands, four measurements
+    auto load_direct = [&](int b, unsigned o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const char *const u = gu + (int64_t)min(b + v, a.batch - 1) * gs;
+            du[v] = at(u, o);
+            dd[v] = at(u + (gd - gu), o);
+        }
+    };
+    auto keep_direct = [&](int b, bool first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const bool live = b + v < a.batch;
+            const float f = first ? wt[b + v] : 1.f;  // the weight goes into a
+            const float2 d{f * (du[v].x + sg * dd[v].x), f * (du[v].y + sg * dd[v].y)};
+            (first ? Ash : Bsh)[v][sid] = live ? d : float2{0.f, 0.f};
+        }
+    };
+    unsigned mine = lane_off(0);                      // folded into the offsets; changes for the last step only
+#pragma unroll
+    for (int j = 0; j < TK; ++j) {
+        xo[j] += mine;
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) yo[j][t] += mine;
+    }
+    // in the order in which the loop waits for them
+#pragma unroll
+    for (int spin = 0; spin < 2; ++spin) {
+#pragma unroll
+        for (int j = 0; j < TK; ++j) x[spin][j] = at((spin != 0) != PP ? gd : gu, xo[j]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) {
+#pragma unroll
+            for (int j = 0; j < TK; ++j) y[spin][j][t] = at(spin ? gd : gu, yo[j][t]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    for (int b = 0; b < a.batch; b += 4) {
+        // an absent measurement multiplies zeros by zeros
+        const bool live = b + par < a.batch;
+        const float f = PP ? wt[b + par] : -wt[b + par];
+#pragma unroll
+        for (int spin = 0; spin < 2; ++spin) {
+            if (!PP) load_direct(b, spin ? bo : ao);
+            // the step after this one (the last loads its own again)
+            const int nb = b + 4 < a.batch ? b + 4 : b;
+            const char *const nu = gu + (int64_t)nb * gs, *const nd = gd + (int64_t)nb * gs;
+            const char *const ny = spin ? nd : nu, *const nx = (spin != 0) != PP ? nd : nu;
+            const unsigned move = spin == 0 ? lane_off(nb) - mine : 0u;
+            mine += move;
+            float xr[TK], xi[TK], xn[TK];
+#pragma unroll
+            for (int j = 0; j < TK; ++j) {
+                xr[j] = live ? f * x[spin][j].x : 0.f;
+                xi[j] = live ? f * x[spin][j].y : 0.f;
+                xn[j] = -xi[j];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < TK; ++j) x[spin][j] = at(nx, xo[j] += move);
+            // a plane's four K2 lie side by side in the rows of G: they are loaded
+            // one right after another, so that the first brings the line for all
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) {
+                float yr[TK], yi[TK];
+#pragma unroll
+                for (int j = 0; j < TK; ++j) {
+                    yr[j] = live ? y[spin][j][t].x : 0.f;
+                    yi[j] = live ? y[spin][j][t].y : 0.f;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < TK; ++j) y[spin][j][t] = at(ny, yo[j][t] += move);
+#pragma unroll
+                for (int j = 0; j < TK; ++j) re[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(yr[j], xr[j], re[j][t], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < TK; ++j) im[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(yi[j], xr[j], im[j][t], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < TK; ++j) re[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(yi[j], xn[j], re[j][t], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < TK; ++j) im[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(yr[j], xi[j], im[j][t], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!PP) keep_direct(b, spin == 0);
+        }
+        if (!PP) {
+            __syncthreads();                          // the four measurements' direct operands are in LDS
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int t = 0; t < TQ; ++t) {
+                    const float2 av = Ash[v][(w * TQ + t) * 16 + (l >> 4) * 4 + lo];
+                    float2 bv[TK];
+#pragma unroll
+                    for (int j = 0; j < TK; ++j) bv[j] = Bsh[v][(j * TQ + t) * 16 + (l & 15)];
+#pragma unroll
+                    for (int j = 0; j < TK; ++j) re[j][t] = __builtin_amdgcn_mfma_f32_4x4x1f32(bv[j].x, av.x, re[j][t], 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < TK; ++j) im[j][t] = __builtin_amdgcn_mfma_f32_4x4x1f32(bv[j].x, av.y, im[j][t], 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < TK; ++j) re[j][t] = __builtin_amdgcn_mfma_f32_4x4x1f32(-bv[j].y, av.y, re[j][t], 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < TK; ++j) im[j][t] = __builtin_amdgcn_mfma_f32_4x4x1f32(bv[j].y, av.x, im[j][t], 0, 0, 0);
+                }
+            __syncthreads();                          // read: the next four's may follow
+        }
+        if ((b + 4) % kMoBatch == 0 || b + 4 >= a.batch) {
+#pragma unroll
+            for (int j = 0; j < TK; ++j)
+#pragma unroll
+                for (int t = 0; t < TQ; ++t) {
+                    rs[j][t] += re[j][t];
+                    is[j][t] += im[j][t];
+                    re[j][t] = im[j][t] = f4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    }
+    if (k1b + w >= n) return;
+    // entry ((p*N + K2)*16 + b3*4 + b4)*side + (K1*4 + b1)*4 + b2; a K2's entries are read together
+    const int h = l >> 4;
+    const int64_t col = (int64_t)(k1b + w) * 16 + (PP ? lo * 4 + h : h * 4 + lo);
+#pragma unroll
+    for (int j = 0; j < TK; ++j) {
+        if (k2b + j >= n) continue;
+        double2 v[TQ][4];
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) {
+            const double2 *row = a.acc + ((((int64_t)min(pb + t, a.planes - 1) * n + k2b + j) * 16 + hi * 4) * a.side + col);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[t][r] = row[r * a.side];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) {
+            if (pb + t >= a.planes) continue;
+            double2 *row = a.acc + ((((int64_t)(pb + t) * n + k2b + j) * 16 + hi * 4) * a.side + col);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[t][r].x += (double)rs[j][t][r];
+                v[t][r].y += (double)is[j][t][r];
+                row[r * a.side] = v[t][r];
+            }
+        }
+    }
+}
+
+// The blocks of a launch of mo_mfma_kernel, a multiple of 8 (one run per XCD).
+int64_t mo_mfma_blocks(const MoArgs &a, int tq) {
+    const int64_t n = a.side / 16;
+    const int64_t s1 = (n + 31) / 32;
+    return ((a.planes + tq - 1) / tq) * s1 * s1 * 64;
+}
+
+// Four orbitals in FP32 fill the 16 x 16 matrix instruction (three use 81 of its
+// 256 products and stay on the vector units); the kernel takes 32-bit byte
+// offsets within four matrices.
+bool mo_uses_mfma(int nb, bool f32, int64_t g_stride) {
+    return f32 && nb == 4 && g_stride * 8 < ((int64_t)1 << 30);
+}
+
 template <typename R>
 hipError_t launch_mo(const MoArgs &a, hipStream_t st) {
     const int64_t n = a.side / ((int64_t)a.nb * a.nb);
@@ -315,6 +574,19 @@ hipError_t launch_mo(const MoArgs &a, hipStream_t st) {
     const int64_t blocks = a.nb <= 8 ? (int64_t)a.planes * n * ((a.side + 255) / 256) : (a.total + 255) / 256;
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
     const dim3 g((unsigned)blocks), b(256);
+    if constexpr (std::is_same<R, float>::value)
+        if (mo_uses_mfma(a.nb, true, a.g_stride)) {
+            const int tq = a.planes > 1 ? 2 : 1;
+            const int64_t mb = mo_mfma_blocks(a, tq);
+            if (mb >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
+            const dim3 gm((unsigned)mb);
+            const bool pp = a.channel == CH_PP;
+            if (tq == 2 && pp) hipLaunchKernelGGL((mo_mfma_kernel<2, true>), gm, b, 0, st, a);
+            else if (tq == 2) hipLaunchKernelGGL((mo_mfma_kernel<2, false>), gm, b, 0, st, a);
+            else if (pp) hipLaunchKernelGGL((mo_mfma_kernel<1, true>), gm, b, 0, st, a);
+            else hipLaunchKernelGGL((mo_mfma_kernel<1, false>), gm, b, 0, st, a);
+            return hipGetLastError();
+        }
     switch (a.nb) {
         case 1: hipLaunchKernelGGL((mo_rows_kernel<R, 1>), g, b, 0, st, a); break;
         case 2: hipLaunchKernelGGL((mo_rows_kernel<R, 2>), g, b, 0, st, a); break;
@@ -374,7 +646,8 @@ extern "C" int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex
         if (!acc[c]) continue;
         for (int64_t p0 = 0; p0 < planes; p0 += kMoPlanes) {
             const int np = (int)std::min<int64_t>(kMoPlanes, planes - p0);
-            for (int b0 = 0; b0 < batch; b0 += kMoBatch) {
+            const int most = mo_uses_mfma(nb, prod == G4_PROD_F32, ngb * ngb) ? kMoLong : kMoBatch;
+            for (int b0 = 0; b0 < batch; b0 += most) {
                 MoArgs a{};
                 a.g_stride = ngb * ngb;
                 const size_t el = prod == G4_PROD_F64 ? 16 : 8;
@@ -385,7 +658,7 @@ extern "C" int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex
                 a.side = side;
                 a.lx = lx; a.ly = ly; a.nw = nw; a.nwg = (int)nwg; a.nb = nb; a.ngb = (int)ngb;
                 a.channel = 1 << c;
-                a.batch = std::min(kMoBatch, batch - b0);
+                a.batch = std::min(most, batch - b0);
                 a.planes = np;
                 for (int i = 0; i < np; ++i) {
                     const int64_t iQ = q_begin + p0 + i;

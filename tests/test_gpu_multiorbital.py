@@ -102,3 +102,29 @@ def test_argument_errors():
         assert e.value.code == g4.G4_E_ARG, kw
     torch.cuda.synchronize()
     assert float(acc.abs().max()) == 0.0
+
+
+# The matrix-instruction kernel (four orbitals, FP32): squares of 32 K cut short, K counts that are not multiples of four,
+# odd plane counts and one plane, batches around its steps of 4, sums of 32 and launches of 128.
+@pytest.mark.parametrize("lx,ly,nw,nwex,q0,q1,count", [(1, 1, 2, 1, 0, 1, 1), (3, 1, 2, 3, 1, 6, 3), (2, 1, 18, 2, 0, 3, 5),
+                                                       (1, 1, 34, 1, 0, 1, 32), (2, 1, 6, 3, 1, 5, 35), (1, 1, 4, 2, 0, 2, 131)])
+def test_four_orbital_matrix_kernel(lx, ly, nw, nwex, q0, q1, count):
+    import torch
+    g4 = g4mod()
+    nb, nq = 4, lx * ly
+    w = Workload("mo4", lx=lx, ly=ly, nw=nw, nwex=nwex, nq=nq, q_begin=q0, q_end=q1)
+    print(f"\ncase mo4 {lx}x{ly} nw={nw} nwex={nwex} planes [{q0}, {q1}) count={count}", flush=True)
+    rng = np.random.default_rng(100 * nw + count)
+    ngb, side = w.ng * nb, w.n * nb * nb
+    gu, gd = (((rng.normal(size=(count, ngb, ngb)) + 1j * rng.normal(size=(count, ngb, ngb))) * 0.3).astype(np.complex64)
+              for _ in range(2))
+    s = np.where(rng.random(count) < 0.8, 1.0, -0.75)
+    du, dd = torch.from_numpy(gu).cuda(), torch.from_numpy(gd).cuda()
+    acc = [torch.full((q1 - q0, side, side), 0.5 + 0.25j, dtype=torch.complex128, device="cuda") for _ in range(3)]
+    g4.g4_accumulate_mo(lx, ly, nw, nwex, nb, nq, None, q0, q1, 7, g4.G4_PROD_F32, du, dd, s, *acc)
+    idx = rng.integers(0, (q1 - q0) * side * side, size=400)
+    for c, a in enumerate(acc):
+        got = a.cpu().numpy().reshape(-1)[idx] - (0.5 + 0.25j)
+        want = ref.entries_mo(w, nb, 1 << c, gu.astype(np.complex128), gd.astype(np.complex128), s, idx)
+        # the FP32 bar of the other multi-orbital cases
+        assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want), c
