@@ -25,7 +25,8 @@ SOURCES = [("g4_abi.cpp", "g4_abi", []), ("g4_kernels.hip", "g4_kernels", []),
            ("g4_gsigma.hip", "g4_gsigma", []), ("g4_multiorbital.hip", "g4_multiorbital", [])] + [
     ("g4_update_inst.hip", "g4_update_k%d_e%d" % (k, e), ["-DG4_KIND=%d" % k, "-DG4_EPT=%d" % e])
     for k in (0, 1, 2) for e in (1, 2, 4, 8)] + [
-    ("g4_update_packed.hip", "g4_update_packed_e%d" % e, ["-DG4_EPT=%d" % e]) for e in (1, 2, 4, 8)]
+    ("g4_update_packed.hip", "g4_update_packed_e%d" % e, ["-DG4_EPT=%d" % e]) for e in (1, 2, 4, 8)] + [
+    ("g4_update_stream.hip", "g4_update_stream_k%d" % k, ["-DG4_KIND=%d" % k]) for k in (0, 1, 2)]
 ARCH = os.environ.get("G4_OFFLOAD_ARCH", "gfx950")
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "g4_internal.hpp"
+#include "g4_stream.hpp"
 
 using namespace g4;
 
@@ -342,13 +343,29 @@ void build_planes(const Plan &P, int nwex, std::vector<int2> &plane_qm) {
     }
 }
 
+// A packed plan whose slice has too few planes to repay the packing of G: the
+// streamed kernel takes the operands from G itself.
+bool streams(const Plan &P, uint32_t channels) {
+    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent && P.d.planes < kStreamPlanes &&
+           stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n);
+}
+
+// The tile order of a plan (see build_work): runs of constant k1 + q for packed
+// operands, windows for register-staged and streamed ones; orbits where the
+// slice has few planes (the same line as for streaming: 14 planes, 6x6, 387 ms a
+// call against 417 in runs; 4 planes, 8x8, 345 against 448).
+int default_order(const Plan &P) {
+    if (P.d.planes < kStreamPlanes) return 4;
+    return uses_pack(P.variant) ? 3 : 2;
+}
+
 // Work decomposition: plane groups (one q, at most mgroup consecutive m) and
 // tiles (group, k1, k2, c0).
 //
 // Tile order.  A tile (k1, k2, q) reads the G block (k2, k1) and the G block
 // (k1+q, k2+q); both lie on the block diagonal of momentum difference
 // d = k1 - k2 (and -d).  Tiles are sorted by the difference class {d, -d};
-// inside a class (order 2, the default) by windows of up to 4 momenta k1 that
+// inside a class (order 2) by windows of up to 4 momenta k1 that
 // are neighbours along a lattice row x 4 consecutive plane groups x half the
 // K2 tiles: k1 + q then stays on one lattice row, so the ~64 tiles an XCD
 // holds at once share about 4 G(K2,K1) blocks and 4 exchange blocks (order 1:
@@ -369,7 +386,7 @@ void spread_over_xcds(const std::vector<int4> &sorted, std::vector<int4> &items)
         }
 }
 
-void build_work(const Plan &P, int nwex, int order, std::vector<int4> &groups,
+void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &groups,
                 std::vector<int4> &items) {
     groups.clear();
     items.clear();
@@ -421,6 +438,51 @@ void build_work(const Plan &P, int nwex, int order, std::vector<int4> &groups,
                             for (int g : groups_of[(size_t)sub(K, k1)])
                                 for (int c = cb; c < std::min(ntile, cb + 2); ++c)
                                     sorted.push_back(int4{g, k1, sub(k1, members[mi]), c * P.tile});
+        }
+        spread_over_xcds(sorted, items);
+        return;
+    }
+    if (order == 4) {
+        // Orbits of (k1, k2) under the slice's momentum transfers: the exchange
+        // block of a tile is the G(K2,K1) block of the tile (k2+q, k1+q), its PP
+        // block that of (q-k1, q-k2), so tiles of one orbit that run together on
+        // an XCD read each block of G once for all three uses.  Inside an orbit
+        // pairs of K2 tiles, then runs of constant k1 + q.
+        std::vector<std::vector<int>> groups_of(d.nc);
+        for (int g = 0; g < ng; ++g) groups_of[(size_t)groups[(size_t)g].x].push_back(g);
+        std::vector<int> qs;
+        for (int q = 0; q < d.nc; ++q)
+            if (!groups_of[(size_t)q].empty()) qs.push_back(q);
+        auto neg = [&](int a) { return sub(0, a); };
+        std::vector<char> seen((size_t)d.nc * d.nc, 0);
+        std::vector<int4> sorted;
+        sorted.reserve((size_t)ng * d.nc * d.nc * ntile);
+        for (int seed = 0; seed < d.nc * d.nc; ++seed) {
+            if (seen[(size_t)seed]) continue;
+            std::vector<int> orbit{seed};
+            seen[(size_t)seed] = 1;
+            for (size_t i = 0; i < orbit.size(); ++i) {
+                const int k1 = orbit[i] % d.nc, k2 = orbit[i] / d.nc;
+                auto visit = [&](int a1, int a2) {
+                    const int e = a2 * d.nc + a1;
+                    if (!seen[(size_t)e]) {
+                        seen[(size_t)e] = 1;
+                        orbit.push_back(e);
+                    }
+                };
+                for (int q : qs) visit(sub(k2, neg(q)), sub(k1, neg(q)));
+                if (pp) for (int q : qs) visit(sub(q, k1), sub(q, k2));
+            }
+            std::vector<int4> run;     // {group, k1, k2, k1 + q}
+            for (int e : orbit)
+                for (int q : qs)
+                    for (int g : groups_of[(size_t)q])
+                        run.push_back(int4{g, e % d.nc, e / d.nc, sub(e % d.nc, neg(q))});
+            std::stable_sort(run.begin(), run.end(), [](const int4 &x, const int4 &y) { return x.w < y.w; });
+            for (int cb = 0; cb < ntile; cb += 2)
+                for (const int4 &t : run)
+                    for (int c = cb; c < std::min(ntile, cb + 2); ++c)
+                        sorted.push_back(int4{t.x, t.y, t.z, c * P.tile});
         }
         spread_over_xcds(sorted, items);
         return;
@@ -642,10 +704,8 @@ int rebuild_work(g4_slice *h) {
         drop_graphs(h);
     }
     std::vector<int4> groups, items;
-    // default order: runs of constant k1 + q for the packed kernels, windows otherwise
-    const bool packed = uses_pack(h->P.variant);
-    const int order = h->order >= 0 ? h->order : (packed ? 3 : 2);
-    build_work(h->P, h->cfg.nwex, order, groups, items);
+    const int order = h->order >= 0 ? h->order : default_order(h->P);
+    build_work(h->P, h->cfg.nwex, order, (h->cfg.channels & G4_PP_UPDOWN) != 0, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     if (items.size() > h->items_cap) {
         G4_HIP(h, hipStreamSynchronize(h->stream));
@@ -675,7 +735,7 @@ void weights_by_value(GatherArgs &ga, const double *sign, int nb, double *ds) {
 // ds: one slice-update kernel launch, counted and, if asked, timed.
 int enqueue_update(g4_slice *h, const GatherArgs &ga, const double *ds, bool timing) {
     const Plan &P = h->P;
-    const bool packed = uses_pack(P.variant);
+    const bool packed = uses_pack(P.variant) && !streams(P, h->cfg.channels);
     UpdateArgs ua;
     ua.gu = ga.gu;
     ua.gd = ga.gd;
@@ -708,7 +768,7 @@ int enqueue_update(g4_slice *h, const GatherArgs &ga, const double *ds, bool tim
         if (rc) return rc;
         G4_HIP(h, hipEventRecord(e0, h->stream));
     }
-    G4_HIP(h, launch_update(P.kind, (int)h->cfg.channels, P.ept, P.mgroup, h->nitems, P.variant, ua, h->stream));
+    G4_HIP(h, launch_update(P.kind, (int)h->cfg.channels, P.ept, P.mgroup, h->nitems, streams(P, h->cfg.channels) ? G4_VARIANT_VALU : P.variant, ua, h->stream));
     if (timing) {
         G4_HIP(h, hipEventRecord(e1, h->stream));
         h->ev_pending.emplace_back(e0, e1);
@@ -752,7 +812,7 @@ int enqueue_pass(g4_slice *h, const void *pu, const void *pd, double *ds, const 
     const int64_t pn = (int64_t)P.d.planes * P.d.n;
     // direct vectors: [slot][b][p][K] in their own buffer, or, for packed
     // operands, inside each measurement's packed block after its G rows
-    const bool packed = uses_pack(P.variant);
+    const bool packed = uses_pack(P.variant) && !streams(P, h->cfg.channels);
     int64_t dir_slot = (int64_t)P.batch * pn, dir_bstride = pn;
     void *dir_a = h->dir;
     if (packed) {
@@ -1022,7 +1082,7 @@ int noalloc_accumulate(const g4_config *cfg, void *const acc[3], const void *G_u
     std::vector<int32_t> qpos(P.d.nc, -1);
     for (size_t i = 0; i < P.qlist.size(); ++i) qpos[(size_t)P.qlist[i]] = (int32_t)i;
     std::vector<int4> groups, items;
-    build_work(P, cfg->nwex, 2, groups, items);
+    build_work(P, cfg->nwex, default_order(P), (cfg->channels & G4_PP_UPDOWN) != 0, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     // workspace layout, 256-byte aligned parts
     auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };
@@ -1195,7 +1255,7 @@ int g4_init_slice(const g4_config *cfg, g4_slice **out) {
     h->cfg.q_list = nullptr;
     h->P = P;
     h->device = cfg->device;
-    if (const char *o = std::getenv("G4_TILE_ORDER")) h->order = std::min(3, std::max(0, std::atoi(o)));
+    if (const char *o = std::getenv("G4_TILE_ORDER")) h->order = std::min(4, std::max(0, std::atoi(o)));
     hipError_t e = hipSetDevice(h->device);
     if (e != hipSuccess) {
         delete h;

@@ -10,6 +10,7 @@
 // D = G_up - G_dn (magnetic) or G_up + G_dn (charge), so the update kernel
 // reads them coalesced instead of gathering diagonals of G per entry.
 #include "g4_internal.hpp"
+#include "g4_stream.hpp"
 
 namespace g4 {
 namespace {
@@ -393,6 +394,23 @@ hipError_t launch_update_mfma(int channels, int slabs, int mgroup, int nitems, s
 G4_PDECL(1) G4_PDECL(2) G4_PDECL(4) G4_PDECL(8)
 #undef G4_PDECL
 
+#define G4_SDECL(k)                                                                                    \
+    hipError_t launch_update_stream_k##k(int channels, int ept, int mgroup, int nitems, size_t lds,   \
+                                         const UpdateArgs &a, hipStream_t s);
+G4_SDECL(0) G4_SDECL(1) G4_SDECL(2)
+#undef G4_SDECL
+
+hipError_t launch_update_stream(int kind, int channels, int ept, int mgroup, int nitems, const UpdateArgs &a,
+                                hipStream_t s) {
+    const size_t lds = stream_lds_bytes(
+        stream_geom(kind == 2 ? 2 : 1, a.d.nw, a.tile < a.d.nw ? a.tile : a.d.nw, mgroup, channels));
+    switch (kind) {
+        case 0: return launch_update_stream_k0(channels, ept, mgroup, nitems, lds, a, s);
+        case 1: return launch_update_stream_k1(channels, ept, mgroup, nitems, lds, a, s);
+        default: return launch_update_stream_k2(channels, ept, mgroup, nitems, lds, a, s);
+    }
+}
+
 hipError_t launch_gather(int prec, const GatherArgs &a, hipStream_t s) {
     if (a.batch > kMaxPassBatch || (!a.slots && !a.sign_out)) return a.slots ? hipErrorInvalidValue : hipSuccess;
     const int64_t total = a.slots ? (int64_t)a.batch * a.d.planes * a.d.n : 1;
@@ -409,6 +427,8 @@ hipError_t launch_update(int kind, int channels, int ept, int mgroup, int nitems
                          const UpdateArgs &a, hipStream_t s) {
     if (nitems == 0) return hipSuccess;
     const size_t lds = update_lds_bytes(kind, channels, a.tile, mgroup, a.d, variant);
+    if (variant == 0 && stream_runs(kind, channels, ept, mgroup, a.tile, a.d, a.dir_slot_stride))
+        return launch_update_stream(kind, channels, ept, mgroup, nitems, a, s);
     if (variant == 1) {
         if (kind != 2 || a.tile != 16 || a.d.nw % 64) return hipErrorInvalidValue;
         return launch_update_mfma(channels, a.d.nw / 64, mgroup, nitems, lds, a, s);
