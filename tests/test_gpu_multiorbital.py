@@ -128,3 +128,19 @@ def test_four_orbital_matrix_kernel(lx, ly, nw, nwex, q0, q1, count):
         want = ref.entries_mo(w, nb, 1 << c, gu.astype(np.complex128), gd.astype(np.complex128), s, idx)
         # the FP32 bar of the other multi-orbital cases
         assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want), c
+
+
+# The two-orbital PH kernel: each channel set, batches around its launches (32 in FP32, 128 in FP64), an accumulator that
+# is not zero, columns that do not fill a block.
+@pytest.mark.parametrize("channels", [1, 2, 3, 7])
+@pytest.mark.parametrize("prod,count", [(0, 1), (0, 130), (1, 2), (1, 33)])
+def test_two_orbital_kernel(channels, prod, count):
+    import torch
+    w, nb = W2.with_(nw=6, q_list=None), 2
+    print(f"\ncase mo2 channels={channels} prod={prod} count={count}", flush=True)
+    gu, gd, s = inputs(w, nb, count, 7 * count + channels)
+    if prod == 1:
+        gu, gd = (g.astype(np.complex64).astype(np.complex128) for g in (gu, gd))
+    got = run(w, nb, channels, prod, gu, gd, s)
+    for ch in got:
+        check_entries(got[ch], ref.accumulate_mo(w, nb, ch, gu, gd, s), 1e-12 if prod == 0 else 1e-6, what="channel %d" % ch)
