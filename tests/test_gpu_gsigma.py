@@ -92,6 +92,32 @@ def test_window_with_a_partial_last_row_block(nw, nwex, c128):
 
 
 @pytest.mark.parametrize("c128", [True, False], ids=["c128", "c64"])
+@pytest.mark.parametrize("lx,ly,nw,nwex,n", [(2, 2, 40, 4, 72), (3, 2, 30, 2, 73), (3, 3, 20, 3, 100), (4, 2, 24, 5, 81),
+                                             (4, 4, 16, 6, 150), (5, 5, 6, 4, 75), (6, 6, 6, 3, 97), (4, 1, 64, 9, 90),
+                                             (5, 3, 18, 2, 76), (8, 8, 4, 2, 256), (2, 2, 10, 1, 400)])
+def test_transform_by_sites(lx, ly, nw, nwex, n, c128):
+    """Lattices whose Fourier sums run in registers and through LDS, column tiles of 48, 64 and 80, sites without a
+    vertex, all vertices on one site, sites given outside the lattice; the last shape is too small for the workspace."""
+    w = Workload("gsig-sites", lx=lx, ly=ly, nw=nw, nwex=nwex, nq=1, beta=5.0, mu=0.1, h=0.2, t=1.0)
+    print(f"\ncase {lx}x{ly} ng={w.ng} n={n} c128={c128}", flush=True)
+    count = 3
+    tau, site, M = expansion_configs(w, 17 + n, count, n)
+    site[1] = lx * ly - 1
+    site[2] = np.where(site[2] == 0, site[2] + (lx * ly > 1), site[2])
+    given = site.copy()
+    given[0, ::3] += lx * ly                          # wraps to the same site
+    got = run(w, 1, tau, given, M, c128)
+    Mo = oracle_inputs(M, c128)
+    rng = np.random.default_rng(n)
+    for b in range(count):
+        idx = rng.integers(0, w.ng * w.ng, size=600)
+        idx[:30] = rng.integers(0, w.ng, size=30) * (w.ng + 1)
+        want = ref.gsigma(w, 1, tau[b], site[b], Mo[b], idx)
+        r, c = idx // w.ng, idx % w.ng
+        assert corr_err(got[b].reshape(-1)[idx], want, g0_diag(w, 1)[r], r == c) <= tol_for(c128, n), b
+
+
+@pytest.mark.parametrize("c128", [True, False], ids=["c128", "c64"])
 def test_no_vertices_gives_g0(c128):
     print(f"\ncase n=0 c128={c128}", flush=True)
     w = TILES
