@@ -346,7 +346,7 @@ void build_planes(const Plan &P, int nwex, std::vector<int2> &plane_qm) {
 // A packed plan whose slice has too few planes to repay the packing of G: the
 // streamed kernel takes the operands from G itself.
 bool streams(const Plan &P, uint32_t channels) {
-    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent && P.d.planes < kStreamPlanes &&
+    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent && stream_packed(P.d.planes, (int)channels) &&
            stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n);
 }
 

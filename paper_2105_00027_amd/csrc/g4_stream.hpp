@@ -55,7 +55,10 @@ inline size_t stream_lds_bytes(const StreamGeom &g) { return (size_t)2 * g.total
 // old kernel otherwise): magnetic, charge and PP, plane groups of 4 and 8, the
 // rows per thread that are compiled; FP32 rows of G have to hold whole pairs of
 // columns; copy offsets are 32-bit within a matrix and within a measurement's
-// direct vectors; both buffers fit the LDS.
+// direct vectors; both buffers fit the LDS.  In FP64 two blocks per CU have to
+// fit where plane groups are of 4: with one, three channels at 64 frequencies
+// took 355 us against the old kernel's 271 (6 momenta of 3 planes, 16
+// measurements); groups of 8 gain with one as well (691 against 990).
 inline bool stream_runs(int kind, int channels, int ept, int mgroup, int tile, const Dims &d, int64_t dir_slot_stride) {
     if ((channels & ~7) || (mgroup != 4 && mgroup != 8)) return false;
     if (ept != 1 && ept != 2 && !(kind == 2 && ept == 4 && mgroup == 4)) return false;
@@ -65,16 +68,22 @@ inline bool stream_runs(int kind, int channels, int ept, int mgroup, int tile, c
     if ((uint64_t)d.ng * d.ng * el >= lim) return false;
     if (((uint64_t)nph * dir_slot_stride + (uint64_t)d.planes * d.n) * el >= lim) return false;
     const StreamGeom g = stream_geom(kind == 2 ? 2 : 1, d.nw, tile < d.nw ? tile : d.nw, mgroup, channels);
-    return stream_fits(g) && stream_lds_bytes(g) <= 160 * 1024;
+    return stream_fits(g) && stream_lds_bytes(g) <= (kind != 2 && mgroup == 4 ? 80 : 160) * 1024;
 }
 hipError_t launch_update_stream(int kind, int channels, int ept, int mgroup, int nitems, const UpdateArgs &a,
                                 hipStream_t s);
 
-// Slices of fewer planes than this run their G4_F_PACKED plan on the streamed
-// kernel: packing G costs the same whatever the slice holds, and each element
-// then serves few entries.  A whole call, packed against streamed: 4 planes of
-// three channels (8x8) 426 : 345 ms, 14 planes (6x6) 447 : 387 ms, 32 planes
-// (4x4) 185 : 189 ms, 128 planes (4x4) 757 : 951 ms.
-constexpr int kStreamPlanes = 32;
+// Small slices run their G4_F_PACKED plan on the streamed kernel: packing G costs
+// the same whatever the slice holds, and each element then serves few entries.
+// Packed against streamed, us per pass of 32 measurements (4x4, 64 frequencies):
+// one channel of 8 planes 555 : 310, 16 planes 696 : 576, 24 planes 838 : 806,
+// 30 planes equal; two channels of 8 planes 661 : 553, 16 planes 1023 : 1138;
+// three channels of 4 planes 632 : 387, and of 8 planes at 6x6 and 32
+// frequencies 1143 : 1480.
+constexpr int kStreamPlanes = 32, kStreamPlaneChannels = 24;
+inline bool stream_packed(int planes, int channels) {
+    const int nch = __builtin_popcount((unsigned)channels);
+    return nch == 1 ? planes < kStreamPlanes : planes * nch < kStreamPlaneChannels;
+}
 
 }  // namespace g4

@@ -43,16 +43,20 @@ __device__ __forceinline__ V cprod(V a, V b) {
     return r;
 }
 
-template <int KIND, int EPT, int MG, int CH>
+// Waves per SIMD the registers are held to: what the LDS allows where that fits
+// without spilling.
+template <int KIND, int EPT, int MG, int CH, int NWC>
 constexpr int stream_waves() {
     constexpr int accs = ChanInfo<CH>::count * EPT * MG;
-    return KIND == 2 ? (accs <= 16 ? 3 : 2) : (accs <= 8 ? 2 : 1);
+    constexpr bool mixed = ChanInfo<CH>::ph && ChanInfo<CH>::pp;
+    if (KIND == 2) return NWC && accs <= 16 && EPT <= 2 && !mixed ? 3 : accs <= 16 || (NWC && accs <= 24 && EPT <= 2) ? 2 : 1;
+    return accs <= 8 || (EPT == 1 && accs <= (NWC ? 16 : 12)) ? 2 : 1;
 }
 
 // NWC: nw fixed at compile time (0: taken from the arguments); the tile is then
 // EPT * 256 / NWC rows and the LDS addresses are one base plus constants.
 template <int KIND, int EPT, int MG, int CH, int NWC>
-__global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH>())) void update_stream_kernel(UpdateArgs a) {
+__global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void update_stream_kernel(UpdateArgs a) {
     using R = typename KindInfo<KIND>::R;
     using V = typename Cx<R>::V;
     using CI = ChanInfo<CH>;
