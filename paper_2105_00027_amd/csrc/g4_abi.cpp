@@ -350,11 +350,17 @@ bool streams(const Plan &P, uint32_t channels) {
            stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n);
 }
 
+// PP singlet and triplet, batched: rows K2 and Q - K2 are summed once (kTileMirror)
+bool pair_rows_once(const Plan &P, uint32_t channels) {
+    return P.kind != 0 && (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) != 0;
+}
+
 // The tile order of a plan (see build_work): runs of constant k1 + q for packed
 // operands, windows for register-staged and streamed ones; orbits where the
 // slice has few planes (the same line as for streaming: 14 planes, 6x6, 387 ms a
 // call against 417 in runs; 4 planes, 8x8, 345 against 448).
-int default_order(const Plan &P) {
+int default_order(const Plan &P, uint32_t channels) {
+    if (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) return pair_rows_once(P, channels) && P.mgroup < 8 ? 4 : 2;
     if (P.d.planes < kStreamPlanes) return 4;
     return uses_pack(P.variant) ? 3 : 2;
 }
@@ -386,8 +392,30 @@ void spread_over_xcds(const std::vector<int4> &sorted, std::vector<int4> &items)
         }
 }
 
-void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &groups,
+// PP singlet and triplet: the tiles left of a whole list where rows K2 and Q - K2
+// are summed once (kTileMirror).  Row i2 of plane m is column i2 of the mirrored
+// list at m + nw - 1 - i2: rows below m have no partner, and a mirrored tile that
+// holds such rows stays, for them alone (kTileEdge).
+void mirror_pairs(const Plan &P, const std::vector<int4> &groups, std::vector<int4> &items) {
+    const Dims &d = P.d;
+    size_t kept = 0;
+    for (int4 it : items) {
+        const int4 g = groups[(size_t)it.x];
+        const int qx = g.x % d.lx, qy = g.x / d.lx, kx = it.z % d.lx, ky = it.z / d.lx;
+        const int k2m = (qx - kx + d.lx) % d.lx + d.lx * ((qy - ky + d.ly) % d.ly);
+        if (it.z < k2m) it.w |= kTileMirror;
+        if (it.z > k2m) {
+            if (it.w >= g.y + g.z - 1) continue;
+            it.w |= kTileEdge;
+        }
+        items[kept++] = it;
+    }
+    items.resize(kept);
+}
+
+void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vector<int4> &groups,
                 std::vector<int4> &items) {
+    const bool pp = (channels & G4_PP_UPDOWN) != 0, pair = pair_rows_once(P, channels);
     groups.clear();
     items.clear();
     const Dims &d = P.d;
@@ -406,6 +434,7 @@ void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &
             for (int k2 = 0; k2 < d.nc; ++k2)
                 for (int k1 = 0; k1 < d.nc; ++k1)
                     for (int c0 = 0; c0 < d.nw; c0 += P.tile) items.push_back(int4{g, k1, k2, c0});
+        if (pair) mirror_pairs(P, groups, items);
         return;
     }
     // difference classes: d and -d together
@@ -414,6 +443,22 @@ void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &
         return (ax - bx + d.lx) % d.lx + d.lx * ((ay - by + d.ly) % d.ly);
     };
     const int ntile = (d.nw + P.tile - 1) / P.tile;
+    if (order == 4 && pair) {
+        // Tiles of the same rows K2 side by side: their G(K2,K1) and G(K2,Q-K1)
+        // are one band of rows of G for every transfer, and the rows Q-K2 of one
+        // transfer one band for every K1 (4x4, 3 planes a transfer, FP64: 5.67 ms
+        // in windows, 4.60 so; plane groups of 8 read more of each band and are
+        // the faster in windows: 12.6 against 13.1 ms)
+        std::vector<int4> sorted;
+        sorted.reserve((size_t)ng * d.nc * d.nc * ntile);
+        for (int k2 = 0; k2 < d.nc; ++k2)
+            for (int c = 0; c < ntile; ++c)
+                for (int g = 0; g < ng; ++g)
+                    for (int k1 = 0; k1 < d.nc; ++k1) sorted.push_back(int4{g, k1, k2, c * P.tile});
+        mirror_pairs(P, groups, sorted);
+        spread_over_xcds(sorted, items);
+        return;
+    }
     if (order == 3) {
         // Inside a class, runs of constant k1 + q: the tiles of a run read the
         // same exchange block (rows k1+q, columns k2+q = k1+q-d), and tiles
@@ -439,6 +484,7 @@ void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &
                                 for (int c = cb; c < std::min(ntile, cb + 2); ++c)
                                     sorted.push_back(int4{g, k1, sub(k1, members[mi]), c * P.tile});
         }
+        if (pair) mirror_pairs(P, groups, sorted);
         spread_over_xcds(sorted, items);
         return;
     }
@@ -484,6 +530,7 @@ void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &
                     for (int c = cb; c < std::min(ntile, cb + 2); ++c)
                         sorted.push_back(int4{t.x, t.y, t.z, c * P.tile});
         }
+        if (pair) mirror_pairs(P, groups, sorted);
         spread_over_xcds(sorted, items);
         return;
     }
@@ -512,6 +559,7 @@ void build_work(const Plan &P, int nwex, int order, bool pp, std::vector<int4> &
                                     sorted.push_back(int4{g, k1, k2, c * P.tile});
                         }
     }
+    if (pair) mirror_pairs(P, groups, sorted);
     spread_over_xcds(sorted, items);
 }
 
@@ -704,8 +752,8 @@ int rebuild_work(g4_slice *h) {
         drop_graphs(h);
     }
     std::vector<int4> groups, items;
-    const int order = h->order >= 0 ? h->order : default_order(h->P);
-    build_work(h->P, h->cfg.nwex, order, (h->cfg.channels & G4_PP_UPDOWN) != 0, groups, items);
+    const int order = h->order >= 0 ? h->order : default_order(h->P, h->cfg.channels);
+    build_work(h->P, h->cfg.nwex, order, h->cfg.channels, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     if (items.size() > h->items_cap) {
         G4_HIP(h, hipStreamSynchronize(h->stream));
@@ -1082,7 +1130,7 @@ int noalloc_accumulate(const g4_config *cfg, void *const acc[3], const void *G_u
     std::vector<int32_t> qpos(P.d.nc, -1);
     for (size_t i = 0; i < P.qlist.size(); ++i) qpos[(size_t)P.qlist[i]] = (int32_t)i;
     std::vector<int4> groups, items;
-    build_work(P, cfg->nwex, default_order(P), (cfg->channels & G4_PP_UPDOWN) != 0, groups, items);
+    build_work(P, cfg->nwex, default_order(P, cfg->channels), cfg->channels, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     // workspace layout, 256-byte aligned parts
     auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };

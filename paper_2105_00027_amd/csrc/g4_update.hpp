@@ -200,10 +200,11 @@ constexpr int NSV = 4;
 // FP32 spin pairs (16 bytes) sit side by side and are read with one 16-byte
 // access; FP64 values are kept in two planes so that consecutive lanes stay
 // 16 bytes apart (no bank conflicts).
-template <typename V, typename CI, int NSG, int NVB>
+template <typename V, typename CI, int NSG, int NVB, bool MIRROR = false>
 struct Tile {
     int nw, nwg, nc, n, planes, ng;
     int q, m_lo, M, p0, k1, k2, c0, T2;
+    int mode, k2m;      // MIRROR (batched PP singlet / triplet): kTileMirror, kTileEdge; the momentum Q - K2
     int yr, yc, zr, zc, nY, nZ, nX, nW, nU, nG, nA, nB, nV;
     int rowY, colY, rowZ, colZ, rowX, colX;
     V *Gp, *Vt;
@@ -226,7 +227,9 @@ struct Tile {
         const int4 it = a.t.items[blockIdx.x];
         const int4 gr = a.t.groups[it.x];
         q = gr.x; m_lo = gr.y; M = gr.z; p0 = gr.w;
-        k1 = it.y; k2 = it.z; c0 = it.w;
+        k1 = it.y; k2 = it.z; c0 = MIRROR ? it.w & (kTileMirror - 1) : it.w;
+        mode = MIRROR ? it.w & ~(kTileMirror - 1) : 0;
+        k2m = MIRROR ? a.t.ksub[q * nc + k2] : 0;
         T2 = min(tile, nw - c0);
         yr = nw + M - 1; yc = T2 + M - 1;
         zr = T2 + M - 1; zc = nw + M - 1;
@@ -369,6 +372,13 @@ struct Tile {
         u = ld(Gp + pu(i));
         d = ld(Gp + pd(i));
     }
+    // MIRROR: whether this tile sums the entry (plane m, row i2l),
+    // and whether it adds the sum to the entry of row Q - K2 as well
+    __device__ __forceinline__ bool sums(int m, int i2l) const { return !MIRROR || !(mode & kTileEdge) || c0 + i2l < m_lo + m; }
+    __device__ __forceinline__ bool mirrors(int m, int i2l) const { return MIRROR && (mode & kTileMirror) && c0 + i2l >= m_lo + m; }
+    __device__ __forceinline__ int64_t mirror_entry(int m, int i2l, int i1) const {
+        return (((int64_t)(p0 + m) * nc + k2m) * nc + k1) * nw * nw + (int64_t)(m_lo + m + nw - 1 - c0 - i2l) * nw + i1;
+    }
     // physical accumulator index (tile-contiguous layout, see update_kernel)
     __device__ __forceinline__ int64_t entry(int m, int i2l, int i1) const {
         return (((int64_t)(p0 + m) * nc + k2) * nc + k1) * nw * nw + (int64_t)(c0 + i2l) * nw + i1;
@@ -390,7 +400,7 @@ __global__ __launch_bounds__(NT, KindInfo<KIND>::waves) void update_kernel(Updat
     constexpr bool PF = KindInfo<KIND>::prefetch;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int tid = threadIdx.x;
-    Tile<V, CI, KindInfo<KIND>::nsg, 1> t;
+    Tile<V, CI, KindInfo<KIND>::nsg, 1, CI::pair && !PF> t;
     t.init(a, a.tile, smem_raw, tid);
     const int nw = t.nw, T2 = t.T2, M = t.M;
     const int RP = NT / nw;            // K2 rows covered by one pass of the block
@@ -533,12 +543,12 @@ __global__ __launch_bounds__(NT, KindInfo<KIND>::waves) void update_kernel(Updat
                 }
             }
         };
-        if (full && r0 + (EPT - 1) * RP < T2) {
+        if (full && r0 + (EPT - 1) * RP < T2 && !(t.mode & kTileEdge)) {
             static_for<0, MG>([&](auto m) { static_for<0, EPT>([&](auto j) { body(j, m); }); });
         } else {
             static_for<0, MG>([&](auto m) {
                 static_for<0, EPT>([&](auto j) {
-                    if (m < M && r0 + j * RP < T2) body(j, m);
+                    if (m < M && r0 + j * RP < T2 && t.sums(m, r0 + j * RP)) body(j, m);
                 });
             });
         }
@@ -546,7 +556,7 @@ __global__ __launch_bounds__(NT, KindInfo<KIND>::waves) void update_kernel(Updat
     if (!act) return;
     static_for<0, EPT>([&](auto j) {
         static_for<0, MG>([&](auto m) {
-            if (!(r0 + j * RP < T2 && m < M)) return;
+            if (!(r0 + j * RP < T2 && m < M && t.sums(m, r0 + j * RP))) return;
             const int64_t e = ebase + m * nn + (int64_t)j * RP * nw;
             if constexpr (PF) {
                 if (CI::mag) acc_st(static_cast<V *>(a.acc[0]) + e, acc[0][j][m]);
@@ -566,6 +576,11 @@ __global__ __launch_bounds__(NT, KindInfo<KIND>::waves) void update_kernel(Updat
                 if (CI::tr) acc_update(a.acc[2], a.acc_kind, e, acc[CI::slot_tr][j][m]);
                 if (CI::ps) acc_update(a.acc[0], a.acc_kind, e, acc[0][j][m]);
                 if (CI::pt) acc_update(a.acc[1], a.acc_kind, e, acc[CI::slot_pt][j][m]);
+                if (CI::pair && t.mirrors(m, r0 + j * RP)) {
+                    const int64_t e2 = t.mirror_entry(m, r0 + j * RP, i1);
+                    if (CI::ps) acc_update(a.acc[0], a.acc_kind, e2, acc[0][j][m]);
+                    if (CI::pt) acc_update(a.acc[1], a.acc_kind, e2, V{-acc[CI::slot_pt][j][m].x, -acc[CI::slot_pt][j][m].y});
+                }
             }
         });
     });

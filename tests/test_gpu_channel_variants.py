@@ -157,3 +157,23 @@ def test_full_size_slice(channels):
         torch.cuda.empty_cache()
     for ch in got:
         check_entries(got[ch], sampled.entries(w, ch, idx, 0, M), 1e-6, what="channel %d" % ch)
+
+
+@pytest.mark.parametrize("w", [
+    Workload("more planes than tile rows", lx=4, ly=1, nw=64, nwex=11, nq=4, q_begin=5, q_end=40, channels=PAIR),
+    Workload("one row per tile", lx=2, ly=1, nw=256, nwex=3, nq=2, q_begin=1, q_end=6, channels=PAIR),
+    Workload("more planes than frequencies", lx=3, ly=1, nw=6, nwex=9, nq=3, q_begin=2, q_end=27, channels=PAIR),
+    Workload("one momentum", lx=1, ly=1, nw=50, nwex=4, nq=1, q_begin=0, q_end=4, channels=PAIR),
+], ids=lambda w: w.name)
+@pytest.mark.parametrize("kind", ["plain", "f64", "f32"])
+def test_pair_rows_summed_once(w, kind):
+    """Rows K2 and Q - K2 share their sum: with and without a partner, odd weights."""
+    print("\ncase %s %s" % (w.name, kind), flush=True)
+    gu, gd, s = host_inputs(w, 3)
+    s = s * np.array([1.0, 0.5, 2.0])
+    if kind == "f32":
+        gu, gd = (x.astype(np.complex64).astype(np.complex128) for x in (gu, gd))
+    kw = {"plain": dict(mode=0), "f64": dict(mode=1, batch=2), "f32": dict(mode=1, prod=1, g_in=1, batch=3)}[kind]
+    g_in = 1 if kind == "f32" else 0
+    got, _ = run_slice(config_for(w, **kw), to_dev(gu, g_in), to_dev(gd, g_in), s)
+    check(got, {ch: ref.accumulate(w, ch, gu, gd, s) for ch in (PS, PT)}, 1e-6 if g_in else 1e-12)
