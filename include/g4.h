@@ -149,7 +149,8 @@ enum {
                                  (16 bytes per element, each momentum block of Nwg columns padded
                                  to a multiple of 8, with the pass's direct vectors) and the
                                  update kernel copies its operand blocks straight from that
-                                 buffer into LDS; needs an even tile and max_batch * (Ng * ldp
+                                 buffer into LDS (slices of few planes: from G itself, with the
+                                 same sizes and rules); needs an even tile and max_batch * (Ng * ldp
                                  * 16 + direct vectors) more device bytes, ldp = Nc * pcb + 1
                                  rounded up to 8, pcb = Nwg rounded up to 8.  Combines with
                                  G4_F_MFMA only (see there). */
@@ -266,7 +267,8 @@ int g4_sync(g4_slice *h);
  * G4_* bit present in cfg.channels) into out_c128 (HOST, 2*count doubles,
  * interleaved).  A compensated accumulator entry is returned as its value in
  * double: the float sum minus the stored compensation term (which holds the
- * negated rounding remainder of the float sum).
+ * negated rounding remainder of the float sum).  Large ranges come through
+ * pinned host buffers (64 MiB in all, kept until g4_destroy) and eight threads.
  * Paper: Background section, the solver workflow (the accumulated G_t is
  * reduced or written out after the last measurement); Implementation section,
  * "Pipeline Ring Algorithm" (the optional write of each rank's part to a
@@ -386,7 +388,9 @@ int g4_accumulate_into(const g4_config *cfg, void *acc_mag, void *acc_chg, void 
  * K = k*(Nw+Nwex-1) + (n + Nw/2) with k = kx_index + lx*ky_index, as for the
  * slice's G input, and the time-ordering conventions folded into M.
  * Computed as E_b M_b E_b^H with E_b(K,i) = e^{i th_i(K)}: phases and g0 in
- * FP64, the two complex products on MFMA in the precision of dtype.
+ * FP64, the two complex products on MFMA in the precision of dtype; where the
+ * vertices are many for the sites, site by site: the products over the times
+ * for each pair of sites and Fourier sums over the lattice.
  * Paper: Background section, the solver workflow (the walker's nonuniform
  * Fourier transform of G_sigma, implemented as matrix-matrix products).
  * Arguments (DEVICE pointers unless noted; all arrays row-major, packed):
@@ -464,7 +468,8 @@ void g4_destroy(g4_slice *h);
  * ("g4 pass: ...", seen by rocprofv3 --marker-trace) when the roctx library
  * is present, G4_ROCTX=0 turns the ranges off.  For measurements,
  * G4_TILE_ORDER=0..4 sets the order of the work tiles and G4_PLANE_GROUP=1|4|8
- * the transfer planes per tile (defaults: by variant; 8, 4 or 1 by Nwex).
+ * the transfer planes per tile (defaults: by variant, channels and planes; 8,
+ * 4 or 1 by Nwex).
  *
  * Message of the last failing call on this host thread ("" if none).
  * Paper: no passage (error reporting of this interface only). */

@@ -19,14 +19,17 @@ LIB = os.path.join(HERE, "libg4.so")
 # (source, object name, extra defines); the update kernel is instantiated once
 # per (kind, K2 rows per thread) pair, the packed-operand kernel once per K2
 # rows per thread
-SOURCES = [("g4_abi.cpp", "g4_abi", []), ("g4_kernels.hip", "g4_kernels", []),
-           ("g4_synth.hip", "g4_synth", []), ("g4_update_mfma.hip", "g4_update_mfma", []),
-           ("g4_direct.hip", "g4_direct", []), ("g4_noalloc.hip", "g4_noalloc", []),
-           ("g4_gsigma.hip", "g4_gsigma", []), ("g4_multiorbital.hip", "g4_multiorbital", [])] + [
+# (longest compilations first)
+SOURCES = [
     ("g4_update_inst.hip", "g4_update_k%d_e%d" % (k, e), ["-DG4_KIND=%d" % k, "-DG4_EPT=%d" % e])
-    for k in (0, 1, 2) for e in (1, 2, 4, 8)] + [
-    ("g4_update_packed.hip", "g4_update_packed_e%d" % e, ["-DG4_EPT=%d" % e]) for e in (1, 2, 4, 8)] + [
-    ("g4_update_stream.hip", "g4_update_stream_k%d" % k, ["-DG4_KIND=%d" % k]) for k in (0, 1, 2)]
+    for e in (8, 4) for k in (0, 1, 2)] + [
+    ("g4_update_packed.hip", "g4_update_packed_e%d" % e, ["-DG4_EPT=%d" % e]) for e in (8, 4, 2, 1)] + [
+    ("g4_update_stream.hip", "g4_update_stream_k%d" % k, ["-DG4_KIND=%d" % k]) for k in (0, 1, 2)] + [
+    ("g4_update_inst.hip", "g4_update_k%d_e%d" % (k, e), ["-DG4_KIND=%d" % k, "-DG4_EPT=%d" % e])
+    for e in (2, 1) for k in (0, 1, 2)] + [
+    ("g4_multiorbital.hip", "g4_multiorbital", []), ("g4_update_mfma.hip", "g4_update_mfma", []),
+    ("g4_gsigma.hip", "g4_gsigma", []), ("g4_abi.cpp", "g4_abi", []), ("g4_kernels.hip", "g4_kernels", []),
+    ("g4_synth.hip", "g4_synth", []), ("g4_direct.hip", "g4_direct", []), ("g4_noalloc.hip", "g4_noalloc", [])]
 ARCH = os.environ.get("G4_OFFLOAD_ARCH", "gfx950")
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

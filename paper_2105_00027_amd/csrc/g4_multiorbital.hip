@@ -11,6 +11,8 @@
 // stored as documented: entry ((p*N + K2)*nb^2 + b3*nb + b4)*(N nb^2) +
 // (K1*nb + b1)*nb + b2, complex128.
 //
+// Four orbitals in FP32 run on the matrix cores (mo_mfma_kernel), and magnetic
+// and charge of two orbitals in one pass (mo_two_kernel); the rest as follows.
 // A launch covers up to 32 measurements of one channel over up to 256 planes
 // and keeps the sums over the measurements in registers, then reads, adds and
 // writes each entry once.  For nb <= 8 (mo_rows_kernel) a thread owns one
@@ -491,13 +493,17 @@ __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
     // Each XCD takes a contiguous run of squares of 8 x 8 blocks (32 K1 x 32 K2,
     // what its CUs hold at once), a square's plane groups one after another: the
     // squares share rows and columns of G in its L2 (runs of all K1 at 8 K2 read
-    // 2.3 times the lines).
-    const int s1 = (n + 31) / 32, gq = (a.planes + TQ - 1) / TQ;
-    const int per = gridDim.x / 8;
-    const int wk = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-    const int in = wk % 64, pb = (wk / 64) % gq * TQ, sq = wk / 64 / gq;
-    const int k1b = (sq % s1 * 8 + in % 8) * 4, k2b = (sq / s1 * 8 + in / 8) * 4;
-    if (k1b >= n || k2b >= n) return;                 // squares past the end
+    // 2.3 times the lines).  Squares past the last K are cut, so that every XCD
+    // has the same number of blocks (40 K, 16 planes, 4 measurements: 137 -> 102 us).
+    const int t4 = (n + 3) / 4, gq = (a.planes + TQ - 1) / TQ;
+    int wk = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+    if (wk >= t4 * t4 * gq) return;
+    const int band = wk / (8 * t4 * gq), bh = min(8, t4 - 8 * band);
+    wk -= band * 8 * t4 * gq;
+    const int sq = wk / (8 * bh * gq), bw = min(8, t4 - 8 * sq);
+    wk -= sq * 8 * bh * gq;
+    const int pb = wk / (bh * bw) * TQ, in = wk % (bh * bw);
+    const int k1b = (sq * 8 + in % bw) * 4, k2b = (band * 8 + in / bw) * 4;
     // past the end the last K, plane and measurement repeat: loaded, never used
     if (tid < kMoLong) wt[tid] = tid < a.batch ? (float)a.sign[tid] : 0.f;
     if (tid < 4 * (TQ + 1) * 2) {
@@ -698,8 +704,17 @@ __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
 // The blocks of a launch of mo_mfma_kernel, a multiple of 8 (one run per XCD).
 int64_t mo_mfma_blocks(const MoArgs &a, int tq) {
     const int64_t n = a.side / 16;
-    const int64_t s1 = (n + 31) / 32;
-    return ((a.planes + tq - 1) / tq) * s1 * s1 * 64;
+    const int64_t t4 = (n + 3) / 4;
+    return ((a.planes + tq - 1) / tq * t4 * t4 + 7) / 8 * 8;
+}
+
+// The blocks of a launch of mo_two_kernel, and whether it runs: both channels of
+// two orbitals in one launch pay at every size, one channel from a block per CU on
+// (2x2, 32 measurements, rows kernel against this one: 60 blocks 28 : 39 us, 96
+// 36 : 45, 256 69 : 54, 512 114 : 79).
+int64_t mo_two_blocks(const MoArgs &a) { return (int64_t)a.planes * (a.side / 8) * ((a.side + 255) / 256); }
+bool mo_uses_two(const MoArgs &a) {
+    return a.nb == 2 && a.channel != CH_PP && (a.channel == (CH_MAG | CH_CHG) || mo_two_blocks(a) >= 256);
 }
 
 // Four orbitals in FP32 fill the 16 x 16 matrix instruction (three use 81 of its
@@ -729,8 +744,8 @@ hipError_t launch_mo(const MoArgs &a, hipStream_t st) {
             else hipLaunchKernelGGL((mo_mfma_kernel<1, false>), gm, b, 0, st, a);
             return hipGetLastError();
         }
-    if (a.nb == 2 && a.channel != CH_PP) {
-        const int64_t tb = (int64_t)a.planes * (n / 2) * ((a.side + 255) / 256);
+    if (mo_uses_two(a)) {
+        const int64_t tb = mo_two_blocks(a);
         if (tb >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
         const dim3 gt((unsigned)tb);
         switch (a.channel) {
@@ -802,7 +817,10 @@ extern "C" int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex
         if (nb == 2 && c == 1 && acc[0]) continue;
         for (int64_t p0 = 0; p0 < planes; p0 += kMoPlanes) {
             const int np = (int)std::min<int64_t>(kMoPlanes, planes - p0);
-            const int most = mo_uses_mfma(nb, prod == G4_PROD_F32, ngb * ngb) || (nb == 2 && c < 2 && prod == G4_PROD_F64)
+            MoArgs shape{};
+            shape.nb = nb; shape.planes = np; shape.side = side;
+            shape.channel = both ? CH_MAG | CH_CHG : 1 << c;
+            const int most = mo_uses_mfma(nb, prod == G4_PROD_F32, ngb * ngb) || (prod == G4_PROD_F64 && mo_uses_two(shape))
                                  ? kMoLong : kMoBatch;
             for (int b0 = 0; b0 < batch; b0 += most) {
                 MoArgs a{};

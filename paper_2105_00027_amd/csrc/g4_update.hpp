@@ -1,5 +1,6 @@
 // Slice-update kernel template for gfx950, included by g4_update_inst.hip,
-// which is compiled once per (kind, K2 rows per thread) pair.
+// which is compiled once per (kind, K2 rows per thread) pair.  Magnetic, charge
+// and PP run g4_update_stream.hip instead wherever stream_runs allows it.
 //
 // Per measurement b (weight s_b) and slice entry (Q, K2, K1):
 //   PH magnetic/charge: s_b [ D(K1+Q,K1) D(K2,K2+Q) - sum_s G_s(K2,K1) G_s(K1+Q,K2+Q) ],

@@ -16,7 +16,7 @@
 // exchange operand is then two 8-byte reads, one per spin, whose lanes (one row
 // apart, odd row pitch) would use every other pair of banks: lanes in which
 // bits 3 and 4 differ take the planes of a pair in the other order (plane m ^ 1
-// at step m, kept in accumulator m until the store), which is the other half of
+// at step m, kept in accumulator m until the epilogue), which is the other half of
 // a chunk, and the reads spread over all banks.
 // Whole 4x4 array, PH magnetic: FP32 passes of 16 measurements 2.80 -> 2.10 ms
 // (5.5 TB/s beyond L2: what bounds it now), FP64 passes of 13 4.1 -> 3.3 ms (the
@@ -42,6 +42,22 @@ __device__ __forceinline__ V cprod(V a, V b) {
     r.y = fma(a.y, b.x, a.x * b.y);
     return r;
 }
+
+// Division of small numbers (e * d < 2^32) by one divisor: a product where the
+// divisor is not known at compile time.  The generic copies do up to 22 of them per
+// thread before the first measurement (54 frequencies, one channel, two
+// measurements a pass: 51.6 -> 49.0 us).
+template <bool CONST>
+struct Div {
+    int d;
+    unsigned m;
+    __device__ __forceinline__ explicit Div(int d_) : d(d_), m(0) {
+        if (!CONST) m = __builtin_amdgcn_readfirstlane(0xffffffffu / (unsigned)d_ + 1);   // 0 for d = 1
+    }
+    __device__ __forceinline__ int operator()(int e) const {
+        return CONST ? e / d : m ? (int)__umulhi((unsigned)e, m) : e;
+    }
+};
 
 // Waves per SIMD the registers are held to: what the LDS allows where that fits
 // without spilling.
@@ -85,55 +101,65 @@ __global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void 
 
     // ---- copies: a part's chunks go in runs of 64, dealt to the waves in turn;
     // rows, columns and planes past the tile's or the group's end repeat its last
-    // one (in bounds, never used).  Both spins have the same offsets.
+    // one (in bounds, never used), and runs of nothing else are left out.  Both spins have the same offsets.
     constexpr StreamGeom gc = stream_geom(EPC, NWC ? NWC : 2, NWC ? EPT * (NT / (NWC ? NWC : 1)) : 2, MG, CH);
     constexpr int KY = !CI::ph ? 0 : NWC ? stream_copies(gc.cY) : kStreamY, KZ = !CI::pp ? 0 : NWC ? stream_copies(gc.cZ) : kStreamZ;
     constexpr int KA = !CI::ph ? 0 : NWC ? stream_copies(gc.cA) : kStreamA, KB = !CI::ph ? 0 : NWC ? stream_copies(gc.cB) : kStreamB;
     const int hp = EPC == 2 ? (min(tile, nw) + 1) / 2 : min(tile, nw);   // chunks of b per plane
     unsigned offY[KY + 1], offZ[KZ + 1], offA[KA + 1], offB[KB + 1];
+    const Div<NWC != 0> divY(g.yp), divZ(g.zn), divA(nw / EPC), divB(hp);
     static_for<0, KY>([&](auto k) {
+        if (!NWC && (k * 4 + wave) * 64 >= g.cY) return;
         const int e = min((k * 4 + wave) * 64 + l, g.cY - 1);
-        const int r = e / g.yp, c = e - r * g.yp;
+        const int r = divY(e), c = e - r * g.yp;
         offY[k] = (unsigned)((rowY + min(r, nw + M - 2)) * ng + colY - sY + min(c, (T2 + M - 2 + sY) / EPC) * EPC) * SV;
     });
     static_for<0, KZ>([&](auto k) {
+        if (!NWC && (k * 4 + wave) * 64 >= g.cZ) return;
         const int e = min((k * 4 + wave) * 64 + l, g.cZ - 1);
-        const int r = e / g.zn, c = e - r * g.zn;
+        const int r = divZ(e), c = e - r * g.zn;
         offZ[k] = (unsigned)((rowZ + min(r, T2 + M - 2)) * ng + colZ - sZ + min(c, (nw + M - 2 + sZ) / EPC) * EPC) * SV;
     });
     static_for<0, KA>([&](auto k) {
+        if (!NWC && (k * 4 + wave) * 64 >= g.cA) return;
         const int e = min((k * 4 + wave) * 64 + l, g.cA - 1), w = nw / EPC;
-        const int sm = e / w, c = e - sm * w, sl = sm / MG, m = min(sm - sl * MG, M - 1);
+        const int sm = divA(e), c = e - sm * w, sl = sm / MG, m = min(sm - sl * MG, M - 1);
         offA[k] = (unsigned)(sl * a.dir_slot_stride + (int64_t)(p0 + m) * n + k1 * nw + c * EPC) * SV;
     });
     static_for<0, KB>([&](auto k) {
+        if (!NWC && (k * 4 + 3 - wave) * 64 >= g.cB) return;
         const int e = min((k * 4 + 3 - wave) * 64 + l, g.cB - 1);
-        const int sm = e / hp, c = e - sm * hp, sl = sm / MG, m = min(sm - sl * MG, M - 1);
+        const int sm = divB(e), c = e - sm * hp, sl = sm / MG, m = min(sm - sl * MG, M - 1);
         offB[k] = (unsigned)(sl * a.dir_slot_stride + (int64_t)(p0 + m) * n + k2 * nw + min(c0 + c * EPC, nw - EPC)) * SV;
     });
+    // ends of the parts: their last row or plane that the group reads
+    const int wA = nw / EPC;
+    const int eY = (nw + M - 1) * g.yp, eZ = (T2 + M - 1) * g.zn;
+    const int eA = ((CI::nph - 1) * MG + M) * wA, eB = ((CI::nph - 1) * MG + M) * hp;
     const unsigned lds_base = (unsigned)(uintptr_t)(lds_t *)smem_raw;
     auto issue = [&](int b) __attribute__((always_inline)) {
         const unsigned buf = lds_base + (b & 1) * bufb;
-        // part of `chunks` chunks from chunk o on, run s by wave w
-        auto part = [&](auto K, const unsigned *off, const char *base, int o, int chunks, int w) __attribute__((always_inline)) {
+        // part of `chunks` chunks from chunk o on, run s by wave w, without the runs
+        // inside [lo, hi): a partial group's planes past the end
+        auto part = [&](auto K, const unsigned *off, const char *base, int o, int chunks, int w, int lo, int hi) __attribute__((always_inline)) {
             static_for<0, decltype(K)::value>([&](auto k) {
                 const int s = k * 4 + w;
-                if (s * 64 < chunks) dma16(base, off[k], buf + (o + s * 64) * 16);
+                if (s * 64 < chunks && !(s * 64 >= lo && s * 64 + 64 <= hi)) dma16(base, off[k], buf + (o + s * 64) * 16);
             });
         };
         const int64_t go = (int64_t)b * a.g_stride * SV, vo = (int64_t)b * a.dir_b_stride * SV;
         const char *const pu = static_cast<const char *>(a.gu) + go, *const pd = static_cast<const char *>(a.gd) + go;
         if constexpr (CI::ph) {
-            part(std::integral_constant<int, KY>{}, offY, pu, 0, g.cY, wave);
-            part(std::integral_constant<int, KY>{}, offY, pd, g.oYd, g.cY, wave);
+            part(std::integral_constant<int, KY>{}, offY, pu, 0, eY, wave, eY, eY);
+            part(std::integral_constant<int, KY>{}, offY, pd, g.oYd, eY, wave, eY, eY);
         }
         if constexpr (CI::pp) {
-            part(std::integral_constant<int, KZ>{}, offZ, pu, g.oZu, g.cZ, wave);
-            part(std::integral_constant<int, KZ>{}, offZ, pd, g.oZd, g.cZ, wave);
+            part(std::integral_constant<int, KZ>{}, offZ, pu, g.oZu, eZ, wave, eZ, eZ);
+            part(std::integral_constant<int, KZ>{}, offZ, pd, g.oZd, eZ, wave, eZ, eZ);
         }
         if constexpr (CI::ph) {
-            part(std::integral_constant<int, KA>{}, offA, static_cast<const char *>(a.dir_a) + vo, g.oA, g.cA, wave);
-            part(std::integral_constant<int, KB>{}, offB, static_cast<const char *>(a.dir_b) + vo, g.oB, g.cB, 3 - wave);
+            part(std::integral_constant<int, KA>{}, offA, static_cast<const char *>(a.dir_a) + vo, g.oA, eA, wave, M * wA, MG * wA);
+            part(std::integral_constant<int, KB>{}, offB, static_cast<const char *>(a.dir_b) + vo, g.oB, eB, 3 - wave, M * hp, MG * hp);
         }
     };
 
@@ -281,11 +307,26 @@ __global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void 
         else run(std::false_type{});
     }
     if (!act) return;
+    // planes back in their places, so that a store instruction's lanes write one
+    // run (4x4, 54 frequencies, 10 planes, magnetic and charge, two measurements a
+    // pass: 262 -> 211 us)
+    if constexpr (SWAP)
+        static_for<0, CI::nph>([&](auto c) {
+            static_for<0, EPT>([&](auto j) {
+                static_for<0, MG / 2>([&](auto h) {
+                    V &p = acc[c][j][2 * h], &q = acc[c][j][2 * h + 1];
+                    const V t = p;
+                    p.x = gx ? q.x : p.x;
+                    p.y = gx ? q.y : p.y;
+                    q.x = gx ? t.x : q.x;
+                    q.y = gx ? t.y : q.y;
+                });
+            });
+        });
     static_for<0, EPT>([&](auto j) {
         static_for<0, MG>([&](auto m) {
             if (r0 + j * RP >= T2) return;
             const int64_t ej = ebase + (int64_t)j * RP * nw;
-            const int pm = m ^ gx;                            // the plane that PH accumulator m holds
             if constexpr (PF) {
                 if (m < M) {
                     const int64_t e = ej + m * nn;
@@ -294,9 +335,9 @@ __global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void 
                     if (CI::pp) acc_st(static_cast<V *>(a.acc[2]) + e, acc[CI::slot_pp][j][m]);
                 }
             } else {
-                if (CI::ph && pm < M) {
-                    if (CI::mag) acc_update(a.acc[0], a.acc_kind, ej + pm * nn, acc[0][j][m]);
-                    if (CI::chg) acc_update(a.acc[1], a.acc_kind, ej + pm * nn, acc[CI::slot_chg][j][m]);
+                if (CI::ph && m < M) {
+                    if (CI::mag) acc_update(a.acc[0], a.acc_kind, ej + m * nn, acc[0][j][m]);
+                    if (CI::chg) acc_update(a.acc[1], a.acc_kind, ej + m * nn, acc[CI::slot_chg][j][m]);
                 }
                 if (CI::pp && m < M) acc_update(a.acc[2], a.acc_kind, ej + m * nn, acc[CI::slot_pp][j][m]);
             }
