@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
     // what its CUs hold at once), a square's plane groups one after another: the
     // squares share rows and columns of G in its L2 (runs of all K1 at 8 K2 read
     // 2.3 times the lines).  Squares past the last K are cut, so that every XCD
-    // has the same number of blocks (40 K, 16 planes, 4 measurements: 137 -> 102 us).
+    // has the same number of blocks (40 K, 16 planes, 4 measurements: 137 -> 104 us).
     const int t4 = (n + 3) / 4, gq = (a.planes + TQ - 1) / TQ;
     int wk = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     if (wk >= t4 * t4 * gq) return;
