@@ -45,8 +45,8 @@ constexpr int kMoPlanes = 256;   // planes per launch
 // 3.27 ms per 64 measurements there, 32 3.18 ms
 constexpr int kMoBatch = 32;
 // measurements per launch of mo_mfma_kernel, which sums kMoBatch at a time and
-// those sums in a second set of registers: one trip of the accumulator to memory
-// and back per 128 measurements
+// those sums in a second set of registers, their roundings kept (in LDS): one trip
+// of the accumulator to memory and back per 128 measurements
 constexpr int kMoLong = 128;
 
 struct MoArgs {
@@ -470,20 +470,29 @@ __global__ __launch_bounds__(256) void mo_two_kernel(MoArgs a) {
 // column l % 4 = b2 and register row b4.  Both run at the full FP32 matrix rate
 // (twice the vector one): 96 matrix cycles per 256 entries and measurement.
 // A wave takes TQ planes x 4 K2 of one K1 (8 accumulator registers a tile, and 8
-// for the sums of every 32 measurements): the column operand G(K2, K1) is loaded
+// for the sums of every 32 measurements; what adding those rounds away is kept as
+// a second float in LDS, 64 KB a block of two planes and still two blocks a CU,
+// and joins the sum in the FP64 accumulator: a launch of 128 measurements gives
+// what four of 32 give): the column operand G(K2, K1) is loaded
 // once for its planes, the row operand once a tile, straight into the lanes that
 // multiply it; each is replaced by the next step's (four measurements, one spin)
 // as soon as it has been used, a whole step ahead.
 // The block's four waves are four neighbouring K1; the direct operands of its
 // 4 K1, 4 K2 and TQ planes are formed once in LDS, four measurements at a time.
 // The 2x2 cluster, Nw = 32, 16 planes, 256 measurements: 13.0 ms on the vector
-// units (eight launches, 30 TFLOP/s), here 7.0 ms (59 TFLOP/s; 2.7 ms at the rate
+// units (eight launches, 30 TFLOP/s), here 7.1 ms (58 TFLOP/s; 2.7 ms at the rate
 // of a large FP32 product).  What is left is the operands' way from L2: runs of
 // four elements (32 bytes); with the row operand always in L1 5.1 ms.
+constexpr int kMoTk = 4;         // K2 of a wave of mo_mfma_kernel
+// dynamic LDS: the low parts of the sums, only where a launch has more than one part
+size_t mo_mfma_lds(int batch, int tq) { return batch > kMoBatch ? (size_t)256 * kMoTk * tq * 2 * 16 : 0; }
+
 template <int TQ, bool PP>
 __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
     typedef float f4 __attribute__((ext_vector_type(4)));
-    constexpr int NB = 4, TK = 4;
+    constexpr int NB = 4, TK = kMoTk;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    f4 *const low = reinterpret_cast<f4 *>(smem_raw) + threadIdx.x;   // [K2][plane][re, im], 256 threads apart
     __shared__ int win1[4], win2[TK], pl1[4][TQ], pl2[TK][TQ];      // window indices of K and of K+Q (PP: Q-K)
     __shared__ float wt[kMoLong];                                   // weights, zeros past the batch
     __shared__ float2 Ash[4][64 * TQ], Bsh[4][64 * TQ];            // [measurement][K of four][plane][orbitals]
@@ -662,12 +671,23 @@ __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
             __syncthreads();                          // read: the next four's may follow
         }
         if ((b + 4) % kMoBatch == 0 || b + 4 >= a.batch) {
+            const int part = b / kMoBatch;
+            // sum + x, its rounding error added to the low part (Knuth's two-sum)
+            auto add = [&](f4 &sum, f4 x, int slot) __attribute__((always_inline)) {
+                if (part == 0) {
+                    sum = x;
+                    return;
+                }
+                const f4 both = sum + x, v = both - sum, err = (sum - (both - v)) + (x - v);
+                low[slot * 256] = part == 1 ? err : low[slot * 256] + err;
+                sum = both;
+            };
 #pragma unroll
             for (int j = 0; j < TK; ++j)
 #pragma unroll
                 for (int t = 0; t < TQ; ++t) {
-                    rs[j][t] += re[j][t];
-                    is[j][t] += im[j][t];
+                    add(rs[j][t], re[j][t], (j * TQ + t) * 2);
+                    add(is[j][t], im[j][t], (j * TQ + t) * 2 + 1);
                     re[j][t] = im[j][t] = f4{0.f, 0.f, 0.f, 0.f};
                 }
         }
@@ -691,10 +711,15 @@ __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
         for (int t = 0; t < TQ; ++t) {
             if (pb + t >= a.planes) continue;
             double2 *row = a.acc + ((((int64_t)(pb + t) * n + k2b + j) * 16 + hi * 4) * a.side + col);
+            f4 lr{0.f, 0.f, 0.f, 0.f}, li = lr;
+            if (a.batch > kMoBatch) {
+                lr = low[((j * TQ + t) * 2) * 256];
+                li = low[((j * TQ + t) * 2 + 1) * 256];
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                v[t][r].x += (double)rs[j][t][r];
-                v[t][r].y += (double)is[j][t][r];
+                v[t][r].x += (double)rs[j][t][r] + (double)lr[r];
+                v[t][r].y += (double)is[j][t][r] + (double)li[r];
                 row[r * a.side] = v[t][r];
             }
         }
@@ -738,11 +763,17 @@ hipError_t launch_mo(const MoArgs &a, hipStream_t st) {
             if (mb >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
             const dim3 gm((unsigned)mb);
             const bool pp = a.channel == CH_PP;
-            if (tq == 2 && pp) hipLaunchKernelGGL((mo_mfma_kernel<2, true>), gm, b, 0, st, a);
-            else if (tq == 2) hipLaunchKernelGGL((mo_mfma_kernel<2, false>), gm, b, 0, st, a);
-            else if (pp) hipLaunchKernelGGL((mo_mfma_kernel<1, true>), gm, b, 0, st, a);
-            else hipLaunchKernelGGL((mo_mfma_kernel<1, false>), gm, b, 0, st, a);
-            return hipGetLastError();
+            const void *const fn = tq == 2 ? (pp ? reinterpret_cast<const void *>(&mo_mfma_kernel<2, true>)
+                                                 : reinterpret_cast<const void *>(&mo_mfma_kernel<2, false>))
+                                           : (pp ? reinterpret_cast<const void *>(&mo_mfma_kernel<1, true>)
+                                                 : reinterpret_cast<const void *>(&mo_mfma_kernel<1, false>));
+            const size_t lds = mo_mfma_lds(a.batch, tq);
+            // beside the kernel's own 9 KB
+            if (lds)
+                if (hipError_t e = ensure_lds_limit(fn, lds + 16 * 1024); e != hipSuccess) return e;
+            MoArgs arg = a;
+            void *params[] = {&arg};
+            return hipLaunchKernel(fn, gm, b, params, lds, st);
         }
     if (mo_uses_two(a)) {
         const int64_t tb = mo_two_blocks(a);

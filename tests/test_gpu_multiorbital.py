@@ -144,3 +144,32 @@ def test_two_orbital_kernel(channels, prod, count):
     got = run(w, nb, channels, prod, gu, gd, s)
     for ch in got:
         check_entries(got[ch], ref.accumulate_mo(w, nb, ch, gu, gd, s), 1e-12 if prod == 0 else 1e-6, what="channel %d" % ch)
+
+
+# The parts of a long launch (sums of 32 measurements in FP32) join in more than FP32: a call gives what calls of 32
+# give, whose sums meet in the complex128 accumulator.  Each of up to three additions rounds away at most 2^-24 of the
+# sum, kept to 2^-24 of itself: 5 * 2^-48 in all, 2^-53 a call on the other side; the bar is 2^-44 of the largest sum.
+@pytest.mark.parametrize("planes,count", [(3, 131), (1, 128), (2, 64), (2, 33)])
+def test_four_orbital_parts_keep_their_width(planes, count):
+    import torch
+    g4 = g4mod()
+    nb, nw = 4, 6
+    w = Workload("mo4-parts", lx=2, ly=1, nw=nw, nwex=3, nq=2, q_begin=0, q_end=planes)
+    print(f"\ncase mo4 parts planes={planes} count={count}", flush=True)
+    rng = np.random.default_rng(7 + count)
+    ngb, side = w.ng * nb, w.n * nb * nb
+    mean = [rng.normal(size=(1, ngb, ngb)) + 1j * rng.normal(size=(1, ngb, ngb)) for _ in range(2)]
+    du, dd = (torch.from_numpy((m + 0.05 * rng.normal(size=(count, ngb, ngb))).astype(np.complex64)).cuda() for m in mean)
+    s = np.ones(count)
+
+    def call(acc, lo, hi):
+        g4.g4_accumulate_mo(2, 1, nw, 3, nb, 2, None, 0, planes, 7, g4.G4_PROD_F32, du[lo:hi], dd[lo:hi], s[lo:hi], *acc)
+
+    zeros = lambda: [torch.zeros((planes, side, side), dtype=torch.complex128, device="cuda") for _ in range(3)]  # noqa: E731
+    whole, parts, largest = zeros(), zeros(), [0.0] * 3
+    call(whole, 0, count)
+    for lo in range(0, count, 32):
+        call(parts, lo, min(lo + 32, count))
+        largest = [max(m, float(torch.view_as_real(a).abs().max())) for m, a in zip(largest, parts)]
+    for c in range(3):
+        assert float(torch.view_as_real(whole[c] - parts[c]).abs().max()) <= 2.0 ** -44 * largest[c], c
