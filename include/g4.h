@@ -170,9 +170,11 @@ enum {
 
 /* slice-update kernel variants (g4_stats, g4_set_plan, g4_tune_result) */
 enum {
-    G4_VARIANT_VALU = 0,      /* operands staged through registers, all terms on the VALU */
+    G4_VARIANT_VALU = 0,      /* all terms on the VALU; operands copied from G into LDS or, for
+                                 shapes that this does not suit, through registers */
     G4_VARIANT_MFMA = 1,      /* G4_F_MFMA */
-    G4_VARIANT_PACKED = 2,    /* G4_F_PACKED */
+    G4_VARIANT_PACKED = 2,    /* G4_F_PACKED (slices of few planes: the kernel of G4_VARIANT_VALU,
+                                 see G4_F_PACKED; g4_autotune times that once, as G4_VARIANT_VALU) */
     G4_VARIANT_PACKED_DEEP = 3, /* G4_F_PACKED_DEEP */
     G4_VARIANT_PACKED_MFMA = 4  /* G4_F_PACKED | G4_F_MFMA */
 };
@@ -215,7 +217,7 @@ typedef struct g4_stats_t {
     uint32_t channels;         /* channel bitmask */
     int32_t batch;             /* measurements per pass in use */
     int32_t tile;              /* K2 rows per tile in use */
-    int32_t variant;           /* kernel variant in use (G4_VARIANT_*) */
+    int32_t variant;           /* plan in use (G4_VARIANT_*); the G4_LOG line names its kernel */
 } g4_stats_t;
 
 /* Fill *cfg with defaults (magnetic channel, c128, FP64, plain, whole
@@ -463,7 +465,9 @@ int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex, int32_t n
 void g4_destroy(g4_slice *h);
 
 /* Environment: G4_LOG=1 prints one line on stderr whenever a slice installs
- * a plan (init, g4_set_plan, g4_autotune); G4_AUTOTUNE_CACHE names the
+ * a plan (init, g4_set_plan, g4_autotune), with the update kernel that its
+ * passes run ("kernel streamed", "registers", "packed", "packed-deep",
+ * "mfma-direct" or "packed-mfma-direct"); G4_AUTOTUNE_CACHE names the
  * autotuner's cache file; each pass of g4_accumulate is a roctx range
  * ("g4 pass: ...", seen by rocprofv3 --marker-trace) when the roctx library
  * is present, G4_ROCTX=0 turns the ranges off.  For measurements,

@@ -350,6 +350,19 @@ bool streams(const Plan &P, uint32_t channels) {
            stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n);
 }
 
+// The slice-update kernel that a pass of a plan runs, by name (G4_LOG, ranges)
+const char *kernel_of(const Plan &P, uint32_t channels) {
+    switch (P.variant) {
+        case G4_VARIANT_MFMA: return "mfma-direct";
+        case G4_VARIANT_PACKED_DEEP: return "packed-deep";
+        case G4_VARIANT_PACKED_MFMA: return "packed-mfma-direct";
+        case G4_VARIANT_PACKED: return streams(P, channels) ? "streamed" : "packed";
+        default:
+            return stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n)
+                       ? "streamed" : "registers";
+    }
+}
+
 // PP singlet and triplet, batched: rows K2 and Q - K2 are summed once (kTileMirror)
 bool pair_rows_once(const Plan &P, uint32_t channels) {
     return P.kind != 0 && (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) != 0;
@@ -647,10 +660,11 @@ void log_plan(const g4_slice *h, const char *why) {
     const Plan &P = h->P;
     static const char *names[] = {"valu", "mfma-direct", "packed", "packed-deep", "packed-mfma-direct"};
     std::fprintf(stderr,
-                 "g4: %s: channels 0x%x, %llu entries per channel, kind %d, variant %s, tile %d, pass %d, "
+                 "g4: %s: channels 0x%x, %llu entries per channel, kind %d, variant %s, kernel %s, tile %d, pass %d, "
                  "rows/thread %d, plane group %d, %d work tiles%s, %llu device bytes\n",
                  why, h->cfg.channels, (unsigned long long)P.entries, P.kind,
-                 P.variant >= 0 && P.variant <= 4 ? names[P.variant] : "?", P.tile, P.batch, P.ept, P.mgroup,
+                 P.variant >= 0 && P.variant <= 4 ? names[P.variant] : "?", kernel_of(P, h->cfg.channels), P.tile,
+                 P.batch, P.ept, P.mgroup,
                  h->nitems, P.persistent ? " (persistent grid)" : "", (unsigned long long)P.total_bytes);
 }
 
@@ -929,7 +943,8 @@ int graph_entry(g4_slice *h, const void *pu, const void *pd, int nb, g4_slice::G
 int run_pass(g4_slice *h, const char *gu, const char *gd, const double *sign, int b0, int nb) {
     const Plan &P = h->P;
     char range[96];
-    std::snprintf(range, sizeof(range), "g4 pass: %d measurements, variant %d, tile %d", nb, P.variant, P.tile);
+    std::snprintf(range, sizeof(range), "g4 pass: %d measurements, variant %d, kernel %s, tile %d", nb, P.variant,
+                  kernel_of(P, h->cfg.channels), P.tile);
     const RoctxRange rr(range);
     const size_t in_el = h->cfg.g_in == G4_IN_C128 ? 16 : 8;
     const int64_t per = (int64_t)P.d.ng * P.d.ng;
@@ -1004,7 +1019,8 @@ int run_plain(g4_slice *h, const char *gu, const char *gd, const double *sign, i
     const uint64_t fit = each ? P.scratch_bytes / each : (uint64_t)kMaxBatch;
     const int group = (int)std::max<uint64_t>(1, std::min<uint64_t>(kMaxBatch, fit));
     char range[96];
-    std::snprintf(range, sizeof(range), "g4 pass: 1 measurements, variant %d, tile %d", P.variant, P.tile);
+    std::snprintf(range, sizeof(range), "g4 pass: 1 measurements, variant %d, kernel %s, tile %d", P.variant,
+                  kernel_of(P, h->cfg.channels), P.tile);
     for (int b0 = 0; b0 < batch; b0 += group) {
         const int nb = std::min(group, batch - b0);
         GatherArgs ga;
@@ -1809,8 +1825,22 @@ int g4_autotune(g4_slice *h, const void *G_up, const void *G_dn, const double *s
                     if (((v == 1 || v == 4) && e > 1) || (v == 3 && e > 2)) continue;
                     cands.push_back({b, v == 1 ? 16 : v == 4 ? 8 : e * (v == 3 ? 512 / h->cfg.nw : rp), v});
                 }
+        // a packed plan that would stream is the VALU plan of the same tile and
+        // pass, timed already
+        auto streams_too = [&](const Cand &c) {
+            if (c.variant != G4_VARIANT_PACKED) return false;
+            g4_config cc = keep_cfg;
+            cc.q_list = keep.qlist.data();
+            cc.flags = with_variant(cc.flags, c.variant);
+            cc.tile = c.tile;
+            Plan P;
+            if (validate(&cc, &P)) return false;
+            P.batch = c.batch;
+            return streams(P, cc.channels);
+        };
         for (const Cand &c : cands) {
             double per = 0.0, err = 0.0;
+            if (streams_too(c)) continue;
             rc = try_plan(c, &per, &err);
             if (rc == G4_E_HIP) return rc;
             if (rc) continue;                    // does not fit this slice
