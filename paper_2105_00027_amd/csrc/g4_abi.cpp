@@ -507,41 +507,79 @@ void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vect
         // block that of (q-k1, q-k2), so tiles of one orbit that run together on
         // an XCD read each block of G once for all three uses.  Inside an orbit
         // pairs of K2 tiles, then runs of constant k1 + q.
-        std::vector<std::vector<int>> groups_of(d.nc);
-        for (int g = 0; g < ng; ++g) groups_of[(size_t)groups[(size_t)g].x].push_back(g);
-        std::vector<int> qs;
-        for (int q = 0; q < d.nc; ++q)
-            if (!groups_of[(size_t)q].empty()) qs.push_back(q);
-        auto neg = [&](int a) { return sub(0, a); };
+        // The list is made on every call of g4_accumulate_into: momenta come from
+        // tables and the runs from a count per target, with no sort of tiles (8x8,
+        // 30 momenta, 8 frequencies: 7.6 -> 1.1 ms a list; the windows take 0.7).
+        std::vector<int> by_q(ng), qs, first;                    // groups by momentum; the momenta; each one's first group
+        for (int g = 0; g < ng; ++g) by_q[(size_t)g] = g;
+        std::stable_sort(by_q.begin(), by_q.end(), [&](int x, int y) { return groups[(size_t)x].x < groups[(size_t)y].x; });
+        for (int i = 0; i < ng; ++i)
+            if (const int q = groups[(size_t)by_q[(size_t)i]].x; qs.empty() || qs.back() != q) {
+                qs.push_back(q);
+                first.push_back(i);
+            }
+        first.push_back(ng);
+        const size_t nq = qs.size();
+        std::vector<int> plus(nq * d.nc), minus(nq * d.nc);      // k + q and q - k, [k][q of qs]
+        for (int k = 0; k < d.nc; ++k)
+            for (size_t i = 0; i < nq; ++i) {
+                minus[k * nq + i] = sub(qs[i], k);
+                plus[k * nq + i] = sub(qs[i], sub(0, k));
+            }
         std::vector<char> seen((size_t)d.nc * d.nc, 0);
-        std::vector<int4> sorted;
-        sorted.reserve((size_t)ng * d.nc * d.nc * ntile);
+        std::vector<int> at(d.nc, 0);                            // per target k1 + q: tiles, then the next one's place
+        std::vector<int2> orbit;                                 // {k1, k2}
+        std::vector<int> targets;
+        std::vector<int4> sorted((size_t)ng * d.nc * d.nc * ntile);
+        size_t base = 0, left = (size_t)d.nc * d.nc;             // the orbit's first tile; pairs not seen yet
         for (int seed = 0; seed < d.nc * d.nc; ++seed) {
             if (seen[(size_t)seed]) continue;
-            std::vector<int> orbit{seed};
             seen[(size_t)seed] = 1;
+            --left;
+            orbit.assign(1, int2{seed % d.nc, seed / d.nc});
+            targets.clear();
+            size_t tiles = 0;
             for (size_t i = 0; i < orbit.size(); ++i) {
-                const int k1 = orbit[i] % d.nc, k2 = orbit[i] / d.nc;
+                const int2 o = orbit[i];
+                const int *const p1 = &plus[o.x * nq], *const p2 = &plus[o.y * nq];
+                const int *const m1 = &minus[o.x * nq], *const m2 = &minus[o.y * nq];
                 auto visit = [&](int a1, int a2) {
-                    const int e = a2 * d.nc + a1;
-                    if (!seen[(size_t)e]) {
-                        seen[(size_t)e] = 1;
-                        orbit.push_back(e);
-                    }
+                    char &s = seen[(size_t)a2 * d.nc + a1];
+                    if (s) return;
+                    s = 1;
+                    --left;
+                    orbit.push_back(int2{a1, a2});
                 };
-                for (int q : qs) visit(sub(k2, neg(q)), sub(k1, neg(q)));
-                if (pp) for (int q : qs) visit(sub(q, k1), sub(q, k2));
+                if (left) {
+                    for (size_t j = 0; j < nq; ++j) visit(p2[j], p1[j]);
+                    if (pp) for (size_t j = 0; j < nq; ++j) visit(m1[j], m2[j]);
+                }
+                for (size_t j = 0; j < nq; ++j) {
+                    int &count = at[(size_t)p1[j]];
+                    if (!count) targets.push_back(p1[j]);
+                    count += first[j + 1] - first[j];
+                }
+                tiles += ng;
             }
-            std::vector<int4> run;     // {group, k1, k2, k1 + q}
-            for (int e : orbit)
-                for (int q : qs)
-                    for (int g : groups_of[(size_t)q])
-                        run.push_back(int4{g, e % d.nc, e / d.nc, sub(e % d.nc, neg(q))});
-            std::stable_sort(run.begin(), run.end(), [](const int4 &x, const int4 &y) { return x.w < y.w; });
-            for (int cb = 0; cb < ntile; cb += 2)
-                for (const int4 &t : run)
-                    for (int c = cb; c < std::min(ntile, cb + 2); ++c)
-                        sorted.push_back(int4{t.x, t.y, t.z, c * P.tile});
+            std::sort(targets.begin(), targets.end());
+            int place = 0;
+            for (int t : targets) {
+                const int here = at[(size_t)t];
+                at[(size_t)t] = place;
+                place += here;
+            }
+            for (const int2 &o : orbit)
+                for (size_t j = 0; j < nq; ++j) {
+                    size_t pl = (size_t)at[(size_t)plus[o.x * nq + j]];
+                    at[(size_t)plus[o.x * nq + j]] += first[j + 1] - first[j];
+                    for (int i = first[j]; i < first[j + 1]; ++i, ++pl)
+                        for (int c = 0; c < ntile; ++c) {
+                            const size_t before = base + (size_t)(c & ~1) * tiles, w = (c | 1) < ntile ? 2 : 1;
+                            sorted[before + pl * w + (c & 1)] = int4{by_q[(size_t)i], o.x, o.y, c * P.tile};
+                        }
+                }
+            base += tiles * ntile;
+            for (int t : targets) at[(size_t)t] = 0;
         }
         if (pair) mirror_pairs(P, groups, sorted);
         spread_over_xcds(sorted, items);

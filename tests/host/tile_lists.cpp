@@ -1,0 +1,100 @@
+// The work-tile list in orbits (order 4) against its plain definition, and its
+// cost against the list in windows (order 2), which g4_accumulate_into made on
+// every call before it.  Exit status 0 when every check holds.
+#include "../../paper_2105_00027_amd/csrc/g4_abi.cpp"
+
+#include <chrono>
+
+namespace {
+
+// Orbits of (k1, k2) in the order of their first pair; a pair's neighbours are
+// (k2+q, k1+q) and, with PP, (q-k1, q-k2); an orbit's tiles by pairs of K2 tiles,
+// then by k1 + q, then as found.
+std::vector<int4> orbits(const Plan &P, const std::vector<int4> &groups, bool pp) {
+    const Dims &d = P.d;
+    auto add = [&](int a, int b) { return (a % d.lx + b % d.lx) % d.lx + d.lx * ((a / d.lx + b / d.lx) % d.ly); };
+    auto sub = [&](int a, int b) {
+        return (a % d.lx - b % d.lx + d.lx) % d.lx + d.lx * ((a / d.lx - b / d.lx + d.ly) % d.ly);
+    };
+    std::vector<int> qs;
+    for (int q = 0; q < d.nc; ++q)
+        for (const int4 &g : groups)
+            if (g.x == q) {
+                qs.push_back(q);
+                break;
+            }
+    std::vector<char> seen((size_t)d.nc * d.nc, 0);
+    std::vector<int4> sorted;
+    for (int seed = 0; seed < d.nc * d.nc; ++seed) {
+        if (seen[(size_t)seed]) continue;
+        std::vector<int> orbit{seed};
+        seen[(size_t)seed] = 1;
+        for (size_t i = 0; i < orbit.size(); ++i) {
+            const int k1 = orbit[i] % d.nc, k2 = orbit[i] / d.nc;
+            std::vector<int> next;
+            for (int q : qs) next.push_back(add(k1, q) * d.nc + add(k2, q));
+            if (pp) for (int q : qs) next.push_back(sub(q, k2) * d.nc + sub(q, k1));
+            for (int e : next)
+                if (!seen[(size_t)e]) {
+                    seen[(size_t)e] = 1;
+                    orbit.push_back(e);
+                }
+        }
+        std::vector<int4> run;
+        for (int e : orbit)
+            for (int q : qs)
+                for (int g = 0; g < (int)groups.size(); ++g)
+                    if (groups[(size_t)g].x == q) run.push_back(int4{g, e % d.nc, e / d.nc, add(e % d.nc, q)});
+        std::stable_sort(run.begin(), run.end(), [](const int4 &x, const int4 &y) { return x.w < y.w; });
+        for (int cb = 0; cb < d.nw; cb += 2 * P.tile)
+            for (const int4 &t : run)
+                for (int c = cb; c < std::min(d.nw, cb + 2 * P.tile); c += P.tile) sorted.push_back(int4{t.x, t.y, t.z, c});
+    }
+    std::vector<int4> items;
+    spread_over_xcds(sorted, items);
+    return items;
+}
+
+double best_us(const Plan &P, int nwex, int order, uint32_t ch) {
+    double best = 1e300;
+    for (int r = 0; r < 30; ++r) {
+        std::vector<int4> groups, items;
+        const auto t = std::chrono::steady_clock::now();
+        build_work(P, nwex, order, ch, groups, items);
+        best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t).count());
+    }
+    return best;
+}
+
+}  // namespace
+
+int main() {
+    struct Shape { int lx, ly, nw, nwex, nq; int64_t q0, q1; uint32_t channels; };
+    const Shape shapes[] = {{1, 1, 16, 3, 1, 0, 3, 1},    {2, 2, 16, 1, 1, 0, 1, 1},   {3, 2, 50, 5, 4, 3, 17, 7},
+                            {4, 4, 8, 2, 16, 0, 30, 4},   {4, 4, 54, 8, 3, 5, 20, 3},  {5, 3, 22, 4, 15, 9, 40, 5},
+                            {6, 6, 8, 1, 36, 0, 30, 7},   {8, 8, 22, 1, 16, 14, 15, 1}, {8, 8, 8, 4, 64, 0, 30, 1},
+                            {8, 8, 8, 1, 64, 0, 30, 1}};
+    int bad = 0;
+    for (const Shape &s : shapes) {
+        g4_config c;
+        g4_config_init(&c);
+        c.lx = s.lx; c.ly = s.ly; c.nw = s.nw; c.nwex = s.nwex; c.nq = s.nq; c.q_begin = s.q0; c.q_end = s.q1;
+        c.channels = s.channels; c.mode = G4_MODE_BATCHED; c.prod = G4_PROD_F32; c.g_in = G4_IN_C64; c.max_batch = 16;
+        Plan P;
+        if (validate(&c, &P) != G4_OK) {
+            std::printf("refused: %s\n", g4_last_error());
+            return 2;
+        }
+        std::vector<int4> groups, items;
+        build_work(P, s.nwex, 4, s.channels, groups, items);
+        const std::vector<int4> want = orbits(P, groups, (s.channels & G4_PP_UPDOWN) != 0);
+        const bool same = items.size() == want.size() && !std::memcmp(items.data(), want.data(), want.size() * sizeof(int4));
+        const double t2 = best_us(P, s.nwex, 2, s.channels), t4 = best_us(P, s.nwex, 4, s.channels);
+        // half as much again as the windows and 10 us for a short list would do; twice that for a busy machine
+        const bool quick = t4 <= 3.0 * t2 + 20.0;
+        std::printf("%dx%d nw %d planes %lld: %zu tiles, windows %.1f us, orbits %.1f us%s%s\n", s.lx, s.ly, s.nw,
+                    (long long)(s.q1 - s.q0), items.size(), t2, t4, same ? "" : "  DIFFERENT", quick ? "" : "  SLOW");
+        bad += !same + !quick;
+    }
+    return bad ? 1 : 0;
+}

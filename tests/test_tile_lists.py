@@ -1,0 +1,23 @@
+"""Work-tile lists (host code): the list in orbits is the one its definition
+gives, and making it costs about what the list in windows costs (it is made on
+every call of g4_accumulate_into)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_orbit_lists(tmp_path):
+    exe = str(tmp_path / "tile_lists")
+    src = [os.path.join(ROOT, "tests", "host", "tile_lists.cpp"),
+           os.path.join(ROOT, "tests", "host_sanitize", "launch_stubs.cpp")]
+    # host-only translation units, as in the sanitizer build of the same code
+    r = subprocess.run(["hipcc", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "include"), *src, "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stdout
