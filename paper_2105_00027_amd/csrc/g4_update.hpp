@@ -36,12 +36,13 @@ template <typename R> struct Cx;
 template <> struct Cx<double> { using V = double2; };
 template <> struct Cx<float> { using V = float2; };
 
-
+// a * b with its roundings spelled out: the update kernels, full and partial
+// tiles, and so slices cut differently, agree bit for bit
 template <typename V>
 __device__ __forceinline__ V cmul(V a, V b) {
     V r;
-    r.x = a.x * b.x - a.y * b.y;
-    r.y = a.x * b.y + a.y * b.x;
+    r.x = fma(-a.y, b.y, a.x * b.x);
+    r.y = fma(a.y, b.x, a.x * b.y);
     return r;
 }
 

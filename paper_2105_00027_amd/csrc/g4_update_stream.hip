@@ -33,16 +33,6 @@ namespace g4 {
 namespace upd {
 namespace {
 
-// a * b with its roundings spelled out: full and partial tiles, and slices cut
-// differently, agree bit for bit
-template <typename V>
-__device__ __forceinline__ V cprod(V a, V b) {
-    V r;
-    r.x = fma(-a.y, b.y, a.x * b.x);
-    r.y = fma(a.y, b.x, a.x * b.y);
-    return r;
-}
-
 // Division of small numbers (e * d < 2^32) by one divisor: a product where the
 // divisor is not known at compile time.  The generic copies do up to 22 of them per
 // thread before the first measurement (54 frequencies, one channel, two
@@ -260,7 +250,7 @@ __global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void 
             static_for<0, EPT>([&](auto j) {
                 if constexpr (CI::nph == 2) {
                     // both PH channels share the exchange sum: computed once
-                    V ex = cprod(xu[j], o.yu[j]);
+                    V ex = cmul(xu[j], o.yu[j]);
                     cmac(ex, xd[j], o.yd[j]);
                     static_for<0, 2>([&](auto c) {
                         V &r = acc[c][j][m];
@@ -278,7 +268,7 @@ __global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void 
                     V &r = acc[CI::slot_pp][j][m];
                     if (CI::ph) {
                         // the PP term takes +s_b: undo the PH negation folded into x
-                        V w = cprod(o.zu[j], xd[j]);
+                        V w = cmul(o.zu[j], xd[j]);
                         cmac(w, o.zd[j], xu[j]);
                         r.x -= w.x;
                         r.y -= w.y;
