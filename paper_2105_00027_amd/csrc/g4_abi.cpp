@@ -528,6 +528,7 @@ void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vect
             }
         std::vector<char> seen((size_t)d.nc * d.nc, 0);
         std::vector<int> at(d.nc, 0);                            // per target k1 + q: tiles, then the next one's place
+        std::vector<int> with_k1(d.nc, 0), k1s;                  // the orbit's pairs by k1, and its k1
         std::vector<int2> orbit;                                 // {k1, k2}
         std::vector<int> targets;
         std::vector<int4> sorted((size_t)ng * d.nc * d.nc * ntile);
@@ -538,9 +539,11 @@ void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vect
             --left;
             orbit.assign(1, int2{seed % d.nc, seed / d.nc});
             targets.clear();
-            size_t tiles = 0;
+            k1s.clear();
             for (size_t i = 0; i < orbit.size(); ++i) {
                 const int2 o = orbit[i];
+                if (!with_k1[(size_t)o.x]++) k1s.push_back(o.x);
+                if (!left) continue;
                 const int *const p1 = &plus[o.x * nq], *const p2 = &plus[o.y * nq];
                 const int *const m1 = &minus[o.x * nq], *const m2 = &minus[o.y * nq];
                 auto visit = [&](int a1, int a2) {
@@ -550,16 +553,18 @@ void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vect
                     --left;
                     orbit.push_back(int2{a1, a2});
                 };
-                if (left) {
-                    for (size_t j = 0; j < nq; ++j) visit(p2[j], p1[j]);
-                    if (pp) for (size_t j = 0; j < nq; ++j) visit(m1[j], m2[j]);
-                }
+                for (size_t j = 0; j < nq; ++j) visit(p2[j], p1[j]);
+                if (pp) for (size_t j = 0; j < nq; ++j) visit(m1[j], m2[j]);
+            }
+            const size_t tiles = orbit.size() * (size_t)ng;
+            for (int k1 : k1s) {
+                const int pairs = with_k1[(size_t)k1];
+                with_k1[(size_t)k1] = 0;
                 for (size_t j = 0; j < nq; ++j) {
-                    int &count = at[(size_t)p1[j]];
-                    if (!count) targets.push_back(p1[j]);
-                    count += first[j + 1] - first[j];
+                    int &count = at[(size_t)plus[k1 * nq + j]];
+                    if (!count) targets.push_back(plus[k1 * nq + j]);
+                    count += pairs * (first[j + 1] - first[j]);
                 }
-                tiles += ng;
             }
             std::sort(targets.begin(), targets.end());
             int place = 0;
@@ -573,7 +578,8 @@ void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vect
                     size_t pl = (size_t)at[(size_t)plus[o.x * nq + j]];
                     at[(size_t)plus[o.x * nq + j]] += first[j + 1] - first[j];
                     for (int i = first[j]; i < first[j + 1]; ++i, ++pl)
-                        for (int c = 0; c < ntile; ++c) {
+                        if (ntile == 1) sorted[base + pl] = int4{by_q[(size_t)i], o.x, o.y, 0};
+                        else for (int c = 0; c < ntile; ++c) {
                             const size_t before = base + (size_t)(c & ~1) * tiles, w = (c | 1) < ntile ? 2 : 1;
                             sorted[before + pl * w + (c & 1)] = int4{by_q[(size_t)i], o.x, o.y, c * P.tile};
                         }
