@@ -347,20 +347,24 @@ void build_planes(const Plan &P, int nwex, std::vector<int2> &plane_qm) {
 // streamed kernel takes the operands from G itself.
 bool streams(const Plan &P, uint32_t channels) {
     return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent && stream_packed(P.d.planes, (int)channels) &&
-           stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n);
+           stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n,
+                       P.batch);
 }
 
-// The slice-update kernel that a pass of a plan runs, by name (G4_LOG, ranges)
-const char *kernel_of(const Plan &P, uint32_t channels) {
-    switch (P.variant) {
-        case G4_VARIANT_MFMA: return "mfma-direct";
-        case G4_VARIANT_PACKED_DEEP: return "packed-deep";
-        case G4_VARIANT_PACKED_MFMA: return "packed-mfma-direct";
-        case G4_VARIANT_PACKED: return streams(P, channels) ? "streamed" : "packed";
-        default:
-            return stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n)
-                       ? "streamed" : "registers";
-    }
+// The variant of launch_update that a pass of nb measurements runs: the plan's,
+// or the streamed kernel.  `slot_stride`: elements between direct-vector slots.
+int pass_variant(const Plan &P, uint32_t channels, int groups, int items, int nb, int64_t slot_stride) {
+    if (P.variant == G4_VARIANT_PACKED) return streams(P, channels) ? kVariantStreamed : P.variant;
+    if (P.variant != G4_VARIANT_VALU) return P.variant;
+    return stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, slot_stride, nb) &&
+                   stream_pays(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, nb, groups, items)
+               ? kVariantStreamed : P.variant;
+}
+
+// Its name (G4_LOG, ranges)
+const char *kernel_name(int variant) {
+    static const char *names[] = {"registers", "mfma-direct", "packed", "packed-deep", "packed-mfma-direct", "streamed"};
+    return variant >= 0 && variant <= kVariantStreamed ? names[variant] : "?";
 }
 
 // PP singlet and triplet, batched: rows K2 and Q - K2 are summed once (kTileMirror)
@@ -697,6 +701,11 @@ int channel_slot(uint32_t channel) {
     }
 }
 
+// The kernel of a pass of nb measurements on a slice (see pass_variant)
+int kernel_of(const g4_slice *h, int nb) {
+    return pass_variant(h->P, h->cfg.channels, h->ngroups, h->nitems, nb, (int64_t)h->P.batch * h->P.d.planes * h->P.d.n);
+}
+
 // G4_LOG=1: one line on stderr whenever a plan is installed.
 void log_plan(const g4_slice *h, const char *why) {
     const char *e = std::getenv("G4_LOG");
@@ -707,8 +716,8 @@ void log_plan(const g4_slice *h, const char *why) {
                  "g4: %s: channels 0x%x, %llu entries per channel, kind %d, variant %s, kernel %s, tile %d, pass %d, "
                  "rows/thread %d, plane group %d, %d work tiles%s, %llu device bytes\n",
                  why, h->cfg.channels, (unsigned long long)P.entries, P.kind,
-                 P.variant >= 0 && P.variant <= 4 ? names[P.variant] : "?", kernel_of(P, h->cfg.channels), P.tile,
-                 P.batch, P.ept, P.mgroup,
+                 P.variant >= 0 && P.variant <= 4 ? names[P.variant] : "?", kernel_name(kernel_of(h, P.batch)),
+                 P.tile, P.batch, P.ept, P.mgroup,
                  h->nitems, P.persistent ? " (persistent grid)" : "", (unsigned long long)P.total_bytes);
 }
 
@@ -874,7 +883,8 @@ int enqueue_update(g4_slice *h, const GatherArgs &ga, const double *ds, bool tim
         if (rc) return rc;
         G4_HIP(h, hipEventRecord(e0, h->stream));
     }
-    G4_HIP(h, launch_update(P.kind, (int)h->cfg.channels, P.ept, P.mgroup, h->nitems, streams(P, h->cfg.channels) ? G4_VARIANT_VALU : P.variant, ua, h->stream));
+    const int variant = pass_variant(P, h->cfg.channels, h->ngroups, h->nitems, ga.batch, ua.dir_slot_stride);
+    G4_HIP(h, launch_update(P.kind, (int)h->cfg.channels, P.ept, P.mgroup, h->nitems, variant, ua, h->stream));
     if (timing) {
         G4_HIP(h, hipEventRecord(e1, h->stream));
         h->ev_pending.emplace_back(e0, e1);
@@ -988,7 +998,7 @@ int run_pass(g4_slice *h, const char *gu, const char *gd, const double *sign, in
     const Plan &P = h->P;
     char range[96];
     std::snprintf(range, sizeof(range), "g4 pass: %d measurements, variant %d, kernel %s, tile %d", nb, P.variant,
-                  kernel_of(P, h->cfg.channels), P.tile);
+                  kernel_name(kernel_of(h, nb)), P.tile);
     const RoctxRange rr(range);
     const size_t in_el = h->cfg.g_in == G4_IN_C128 ? 16 : 8;
     const int64_t per = (int64_t)P.d.ng * P.d.ng;
@@ -1064,7 +1074,7 @@ int run_plain(g4_slice *h, const char *gu, const char *gd, const double *sign, i
     const int group = (int)std::max<uint64_t>(1, std::min<uint64_t>(kMaxBatch, fit));
     char range[96];
     std::snprintf(range, sizeof(range), "g4 pass: 1 measurements, variant %d, kernel %s, tile %d", P.variant,
-                  kernel_of(P, h->cfg.channels), P.tile);
+                  kernel_name(kernel_of(h, 1)), P.tile);
     for (int b0 = 0; b0 < batch; b0 += group) {
         const int nb = std::min(group, batch - b0);
         GatherArgs ga;
@@ -1295,7 +1305,8 @@ int noalloc_accumulate(const g4_config *cfg, void *const acc[3], const void *G_u
         ua.persistent = P.persistent;
         ua.d = P.d;
         ua.t = t;
-        G4_NA(launch_update(P.kind, (int)cfg->channels, P.ept, P.mgroup, (int)items.size(), P.variant, ua, st));
+        const int variant = pass_variant(P, cfg->channels, (int)groups.size(), (int)items.size(), nb, ua.dir_slot_stride);
+        G4_NA(launch_update(P.kind, (int)cfg->channels, P.ept, P.mgroup, (int)items.size(), variant, ua, st));
     }
     G4_NA(hipStreamSynchronize(st));
 #undef G4_NA

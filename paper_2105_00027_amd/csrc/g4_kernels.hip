@@ -402,8 +402,7 @@ G4_SDECL(0) G4_SDECL(1) G4_SDECL(2)
 
 hipError_t launch_update_stream(int kind, int channels, int ept, int mgroup, int nitems, const UpdateArgs &a,
                                 hipStream_t s) {
-    const size_t lds = stream_lds_bytes(
-        stream_geom(kind == 2 ? 2 : 1, a.d.nw, a.tile < a.d.nw ? a.tile : a.d.nw, mgroup, channels));
+    const size_t lds = stream_lds_bytes(stream_geom_of(kind, channels, mgroup, a.tile, a.d), a.batch);
     switch (kind) {
         case 0: return launch_update_stream_k0(channels, ept, mgroup, nitems, lds, a, s);
         case 1: return launch_update_stream_k1(channels, ept, mgroup, nitems, lds, a, s);
@@ -427,8 +426,10 @@ hipError_t launch_update(int kind, int channels, int ept, int mgroup, int nitems
                          const UpdateArgs &a, hipStream_t s) {
     if (nitems == 0) return hipSuccess;
     const size_t lds = update_lds_bytes(kind, channels, a.tile, mgroup, a.d, variant);
-    if (variant == 0 && stream_runs(kind, channels, ept, mgroup, a.tile, a.d, a.dir_slot_stride))
+    if (variant == kVariantStreamed) {
+        if (!stream_runs(kind, channels, ept, mgroup, a.tile, a.d, a.dir_slot_stride, a.batch)) return hipErrorInvalidValue;
         return launch_update_stream(kind, channels, ept, mgroup, nitems, a, s);
+    }
     if (variant == 1) {
         if (kind != 2 || a.tile != 16 || a.d.nw % 64) return hipErrorInvalidValue;
         return launch_update_mfma(channels, a.d.nw / 64, mgroup, nitems, lds, a, s);

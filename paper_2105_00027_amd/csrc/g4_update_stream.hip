@@ -75,7 +75,7 @@ __global__ __launch_bounds__(NT, (stream_waves<KIND, EPT, MG, CH, NWC>())) void 
     const int tile = NWC ? EPT * (NT / NWC) : a.tile;
     const StreamGeom g = stream_geom(EPC, nw, min(tile, nw), MG, CH);   // a full tile's, for all tiles
     const int bufb = g.total * 16;
-    R *sg = reinterpret_cast<R *>(smem_raw + 2 * bufb);
+    R *sg = reinterpret_cast<R *>(smem_raw + stream_buffers(a.batch) * bufb);
     if (tid < a.batch) sg[tid] = (R)a.sign[tid];
 
     const int4 it = a.t.items[blockIdx.x];

@@ -29,15 +29,32 @@ def kernels(capfd, monkeypatch, cfg, act=lambda h: None):
 
 
 @pytest.mark.parametrize("w,kw,want", [
-    (W, dict(mode=1, batch=4), "streamed"), (W, F32, "streamed"),
-    (W.with_(channels=8), F32, "registers"), (W.with_(nwex=7, lx=3), F32, "streamed"),
-    (W.with_(nwex=8, lx=3), F32, "registers"),                               # odd Ng
+    (W, dict(mode=1, batch=4), "streamed"), (W, dict(F32, batch=8), "streamed"),
+    (W.with_(channels=8), dict(F32, batch=8), "registers"), (W.with_(nwex=7, lx=3), dict(F32, batch=8), "streamed"),
+    (W.with_(nwex=8, lx=3), dict(F32, batch=8), "registers"),                # odd Ng
     (W, dict(F32, flags=16), "streamed"), (MANY, dict(F32, flags=16), "packed"),
     (W.with_(channels=3), dict(F32, flags=16), "streamed"), (W.with_(channels=7), dict(F32, flags=16), "packed"),
     (W, dict(F32, flags=16 | 64), "packed"), (W, dict(F32, prod=2, flags=16), "packed"),
     (W, dict(F32, flags=32), "packed-deep"), (W.with_(nw=64), dict(F32, flags=8), "mfma-direct"),
     (W.with_(nw=64), dict(F32, flags=24), "packed-mfma-direct")])
 def test_plan_line_names_the_kernel(capfd, monkeypatch, w, kw, want):
+    print(f"\ncase {w} {kw}", flush=True)
+    assert kernels(capfd, monkeypatch, config_for(w, **kw)) == [want]
+
+
+G128 = Workload("nw 128", lx=2, ly=1, nw=128, nwex=8, nq=2, q_begin=0, q_end=8)
+
+
+# Fewer blocks a CU than the register-staged kernel: two buffers of a batched pass at 128 frequencies (a launch of one
+# measurement has one buffer), three channels there; plane groups that are mostly empty; 8 frequencies.
+@pytest.mark.parametrize("w,kw,want", [
+    (G128, dict(mode=0), "streamed"), (G128, dict(mode=1, batch=1), "streamed"), (G128, dict(mode=1, batch=4), "registers"),
+    (G128.with_(channels=7), F32, "registers"), (G128.with_(channels=7), dict(F32, batch=1), "registers"),
+    (G128.with_(channels=7, nw=64), F32, "streamed"), (G128.with_(nw=64, q_end=1), dict(mode=0), "streamed"),
+    (G128.with_(nw=54, q_end=2), dict(mode=0), "registers"), (G128.with_(nw=54, q_end=8), dict(mode=0), "streamed"),
+    (G128.with_(nw=54, q_end=8), dict(F32, batch=8), "streamed"), (G128.with_(nw=54, q_end=8), F32, "registers"),
+    (G128.with_(nw=54, q_end=3), dict(F32, batch=8), "registers"), (G128.with_(nw=8), dict(mode=0), "registers")])
+def test_default_plan_kernel(capfd, monkeypatch, w, kw, want):
     print(f"\ncase {w} {kw}", flush=True)
     assert kernels(capfd, monkeypatch, config_for(w, **kw)) == [want]
 

@@ -1,6 +1,7 @@
-"""Work-tile lists (host code): the list in orbits is the one its definition
+"""Host code of the plans: the tile list in orbits is the one its definition
 gives, and making it costs about what the list in windows costs (it is made on
-every call of g4_accumulate_into)."""
+every call of g4_accumulate_into); the routes of launches to kernels hold over
+many shapes."""
 import os
 import shutil
 import subprocess
@@ -11,9 +12,10 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
-def test_orbit_lists(tmp_path):
-    exe = str(tmp_path / "tile_lists")
-    src = [os.path.join(ROOT, "tests", "host", "tile_lists.cpp"),
+@pytest.mark.parametrize("driver", ["tile_lists", "kernel_routes"])
+def test_host_driver(tmp_path, driver):
+    exe = str(tmp_path / driver)
+    src = [os.path.join(ROOT, "tests", "host", driver + ".cpp"),
            os.path.join(ROOT, "tests", "host_sanitize", "launch_stubs.cpp")]
     # host-only translation units, as in the sanitizer build of the same code
     r = subprocess.run(["hipcc", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "include"), *src, "-o", exe],
