@@ -343,10 +343,19 @@ void build_planes(const Plan &P, int nwex, std::vector<int2> &plane_qm) {
     }
 }
 
+// Plane groups of a slice (see build_work)
+int plane_groups(const Plan &P) {
+    int n = 0;
+    const int64_t nwex = P.d.nwex, end = P.d.q_begin + P.d.planes;
+    for (int64_t iQ = P.d.q_begin; iQ < end; ++n) iQ = std::min({end, (iQ / nwex + 1) * nwex, iQ + P.mgroup});
+    return n;
+}
+
 // A packed plan whose slice has too few planes to repay the packing of G: the
 // streamed kernel takes the operands from G itself.
 bool streams(const Plan &P, uint32_t channels) {
-    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent && stream_packed(P.d.planes, (int)channels) &&
+    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent &&
+           stream_packed((int)channels, P.ept, P.mgroup, P.tile, P.d, P.batch, plane_groups(P)) &&
            stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n,
                        P.batch);
 }
@@ -372,32 +381,28 @@ bool pair_rows_once(const Plan &P, uint32_t channels) {
     return P.kind != 0 && (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) != 0;
 }
 
-// Plane groups of a slice (see build_work)
-int plane_groups(const Plan &P, int nwex) {
-    int n = 0;
-    const int64_t end = P.d.q_begin + P.d.planes;
-    for (int64_t iQ = P.d.q_begin; iQ < end; ++n) iQ = std::min({end, (iQ / nwex + 1) * nwex, iQ + P.mgroup});
-    return n;
-}
-
 // The tile order of a plan (see build_work): runs of constant k1 + q for packed
-// operands, windows for register-staged and streamed ones; orbits (on 6996 random
-// shapes, windows over orbits with the streamed kernel, median, 5% lowest and
-// highest; the others are like it)
-//   where the slice is one plane group, whose matrices exceed an XCD's L2: 1.02
-//     (0.98, 1.20), three channels at 8x8 1.6;
-//   of several groups, whose pairs of transfers spread an orbit wider than an L2,
-//     where the passes are long, FP32, of one PH channel and on large clusters and
-//     matrices: 1.03 (0.91, 1.17), the 6x6 share of 14 planes 1.05.
+// operands, windows for register-staged and streamed ones; or orbits (on 6996
+// random shapes, windows over orbits with the streamed kernel, or runs over orbits
+// with the packed one, median, 5% lowest and highest)
+//   packed operands of fewer than 32 planes: 1.01 (0.96, 1.13);
+//   one plane group, whose matrices exceed an XCD's L2: 1.02 (0.98, 1.20), the 8x8
+//     three-channel share 1.6;
+//   several groups, whose transfers spread an orbit wider than an L2, in long FP32
+//     passes of PH channels on large clusters and matrices: 1.03 (0.91, 1.17), the
+//     6x6 share of 14 planes 1.05.
 // Several groups otherwise lose: 0.99 (0.88, 1.06), three channels of 128
 // frequencies at 6x6 0.70.
-int default_order(const Plan &P, int nwex, uint32_t channels) {
+int default_order(const Plan &P, uint32_t channels) {
     if (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) return pair_rows_once(P, channels) && P.mgroup < 8 ? 4 : 2;
     const Dims &d = P.d;
+    const bool streamed = streams(P, channels);
+    if (uses_pack(P.variant) && !streamed) return d.planes < 32 ? 4 : 3;
     const double pair = 2.0 * d.ng * d.ng * (P.kind == 2 ? 8 : 16);   // bytes of both spins' matrices
-    const bool long_ph = P.kind == 2 && (channels == G4_PH_MAGNETIC || channels == G4_PH_CHARGE) && P.batch >= 8;
-    if (plane_groups(P, nwex) == 1 ? pair > 4e6 : long_ph && d.nc >= 32 && d.planes < 32 && pair > 32e6) return 4;
-    return uses_pack(P.variant) && !streams(P, channels) ? 3 : 2;
+    if (plane_groups(P) == 1) return pair > 4e6 ? 4 : 2;
+    const bool ph = channels == G4_PH_MAGNETIC || channels == G4_PH_CHARGE ||
+                    (streamed && channels == (G4_PH_MAGNETIC | G4_PH_CHARGE));
+    return ph && P.kind == 2 && d.nc >= 32 && d.planes < 32 && (P.batch >= 32 ? pair > 16e6 : P.batch >= 8 && pair > 32e6) ? 4 : 2;
 }
 
 // Work decomposition: plane groups (one q, at most mgroup consecutive m) and
@@ -837,7 +842,7 @@ int rebuild_work(g4_slice *h) {
         drop_graphs(h);
     }
     std::vector<int4> groups, items;
-    const int order = h->order >= 0 ? h->order : default_order(h->P, h->cfg.nwex, h->cfg.channels);
+    const int order = h->order >= 0 ? h->order : default_order(h->P, h->cfg.channels);
     build_work(h->P, h->cfg.nwex, order, h->cfg.channels, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     if (items.size() > h->items_cap) {
@@ -1218,7 +1223,7 @@ int noalloc_accumulate(const g4_config *cfg, void *const acc[3], const void *G_u
     std::vector<int32_t> qpos(P.d.nc, -1);
     for (size_t i = 0; i < P.qlist.size(); ++i) qpos[(size_t)P.qlist[i]] = (int32_t)i;
     std::vector<int4> groups, items;
-    build_work(P, cfg->nwex, default_order(P, cfg->nwex, cfg->channels), cfg->channels, groups, items);
+    build_work(P, cfg->nwex, default_order(P, cfg->channels), cfg->channels, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     // workspace layout, 256-byte aligned parts
     auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };

@@ -151,17 +151,46 @@ constexpr int kVariantStreamed = 5;
 hipError_t launch_update_stream(int kind, int channels, int ept, int mgroup, int nitems, const UpdateArgs &a,
                                 hipStream_t s);
 
-// Small slices run their G4_F_PACKED plan on the streamed kernel: packing G costs
-// the same whatever the slice holds, and each element then serves few entries.
-// Packed against streamed, us per pass of 32 measurements (4x4, 64 frequencies):
-// one channel of 8 planes 555 : 310, 16 planes 696 : 576, 24 planes 838 : 806,
-// 30 planes equal; two channels of 8 planes 661 : 553, 16 planes 1023 : 1138;
-// three channels of 4 planes 632 : 387, and of 8 planes at 6x6 and 32
-// frequencies 1143 : 1480.
-constexpr int kStreamPlanes = 32, kStreamPlaneChannels = 24;
-inline bool stream_packed(int planes, int channels) {
-    const int nch = __builtin_popcount((unsigned)channels);
-    return nch == 1 ? planes < kStreamPlanes : planes * nch < kStreamPlaneChannels;
+// Whether a G4_F_PACKED plan of passes of `batch` measurements leaves the packing
+// out and runs the streamed kernel: packing G costs the same whatever the slice
+// holds, and each element then serves few entries.  Both were timed on 7269 random
+// shapes; packed time over streamed, median (5% lowest), of those below that stream
+// and of those that pack:
+//   PP alone                                        1.37 (0.97)   1.15 (0.98)
+//   one PH channel, plane groups of 4               1.28 (1.03)   1.07 (0.80)
+//     groups of 8, 64 frequencies (compiled in)     1.36 (1.04)   1.07 (0.77)
+//     groups of 8, others                           1.34 (0.98)   0.92 (0.73)
+//   several channels, 64 frequencies                1.46 (1.17)   1.21 (0.97)
+//   magnetic and charge, others                     1.21 (0.91)   0.87 (0.62)
+//   PH and PP, others                               1.17 (0.84)   0.90 (0.61)
+//   three, others                                   1.15 (0.88)   0.91 (0.55)
+// (the first lines pack above the plane counts to which streaming was tried), and
+// long passes over less than 1 MB of G pack: few tiles, each waiting for its own
+// copies (0.93, 0.72).  Streaming wants few plane groups (each reads its blocks of G
+// again), two blocks a CU, and long passes, as more copies then hide behind sums.
+inline bool stream_packed(int channels, int ept, int mgroup, int tile, const Dims &d, int batch, int groups) {
+    if (batch >= 16 && 2.0 * d.ng * d.ng * 8 < 1e6) return false;
+    const int nch = __builtin_popcount((unsigned)channels), p = d.planes;
+    const int blocks = stream_blocks(2, channels, ept, mgroup, tile, d, batch);
+    const bool pp = (channels & CH_PP) != 0, nw64 = d.nw == 64 && tile == ept * 4, two = blocks >= 2;
+    if (nch == 1) {
+        if (pp) return p < 32;
+        if (mgroup == 4) return p < (batch <= 24 ? 32 : d.nc >= 16 ? 17 : 13);
+        if (nw64) return p < (batch <= 24 ? 32 : 20);
+        if (d.nw < 20 && blocks >= 3) return p < 24;
+        return p < 4 || (two && groups <= 2 && (batch > 2 || d.nw < 20));
+    }
+    if (p * nch >= 24) return false;
+    if (nw64) return true;
+    if (!pp) {                                   // magnetic and charge
+        if (p <= 2) return true;
+        if (!two) return false;
+        if (p <= 5) return batch >= 8 || d.nw >= 48;
+        return groups == 1 || (groups == 2 && (d.nc < 16 || batch >= 32)) || d.nw >= 128 || (d.nw < 20 && blocks >= 3);
+    }
+    if (!two) return nch == 2 ? p <= 1 : mgroup == 8 && p <= 3;
+    if (nch == 2) return p <= 5 || (groups == 1 && batch >= 8);
+    return groups <= 2 && (p <= 4 || (mgroup == 8 && groups == 1 && (batch >= 8 || tile <= 7)));
 }
 
 }  // namespace g4

@@ -99,14 +99,15 @@ int main() {
                     (long long)(s.q1 - s.q0), items.size(), t2, t4, same ? "" : "  DIFFERENT", quick ? "" : "  SLOW");
         bad += !same + !quick;
     }
-    // the order of a plan: orbits for one plane group beyond an L2, or long FP32 passes of one PH channel on large
-    // clusters; windows (runs for packed operands) otherwise
+    // the order of a plan: orbits for one plane group beyond an L2, long FP32 passes of PH channels on large clusters
+    // and few planes of packed operands; windows (runs for packed operands) otherwise
     struct Order { int l, nw, nwex, nq; int64_t q0, q1; uint32_t channels; int prod, batch; uint32_t flags; int want; };
     const Order orders[] = {{8, 64, 4, 64, 64, 68, 7, 1, 32, G4_F_PACKED, 4}, {6, 64, 8, 5, 13, 27, 1, 1, 16, G4_F_PACKED, 4},
                             {6, 64, 8, 5, 13, 27, 1, 1, 2, 0, 2},             {6, 64, 8, 5, 13, 27, 3, 1, 16, 0, 2},
                             {6, 128, 16, 36, 3, 14, 7, 1, 16, 0, 2},          {6, 54, 16, 36, 3, 14, 1, 0, 4, 0, 2},
                             {4, 64, 8, 16, 0, 16, 1, 1, 64, 0, 2},            {4, 128, 8, 16, 0, 8, 1, 0, 8, 0, 4},
                             {2, 16, 8, 4, 0, 8, 1, 0, 8, 0, 2},               {4, 64, 8, 16, 0, 128, 1, 1, 64, G4_F_PACKED, 3},
+                            {4, 64, 8, 16, 0, 31, 1, 1, 64, G4_F_PACKED, 4},  {6, 32, 4, 36, 0, 8, 1, 1, 64, G4_F_PACKED, 4},
                             {6, 64, 8, 5, 13, 27, 24, 1, 16, 0, 2}};
     for (const Order &o : orders) {
         g4_config c;
@@ -115,10 +116,10 @@ int main() {
         c.channels = o.channels; c.mode = G4_MODE_BATCHED; c.prod = o.prod; c.g_in = o.prod ? G4_IN_C64 : G4_IN_C128;
         c.max_batch = o.batch; c.flags = o.flags;
         Plan P;
-        const int got = validate(&c, &P) == G4_OK ? default_order(P, c.nwex, c.channels) : -1;
+        const int got = validate(&c, &P) == G4_OK ? default_order(P, c.channels) : -1;
         std::vector<int4> groups, items;
         if (got >= 0) build_work(P, c.nwex, got, c.channels, groups, items);
-        if (got != o.want || plane_groups(P, c.nwex) != (int)groups.size()) {
+        if (got != o.want || plane_groups(P) != (int)groups.size()) {
             std::printf("%dx%d nw %d planes %lld channels %u: order %d, not %d\n", o.l, o.l, o.nw, (long long)(o.q1 - o.q0),
                         o.channels, got, o.want);
             ++bad;

@@ -33,7 +33,16 @@ def kernels(capfd, monkeypatch, cfg, act=lambda h: None):
     (W.with_(channels=8), dict(F32, batch=8), "registers"), (W.with_(nwex=7, lx=3), dict(F32, batch=8), "streamed"),
     (W.with_(nwex=8, lx=3), dict(F32, batch=8), "registers"),                # odd Ng
     (W, dict(F32, flags=16), "streamed"), (MANY, dict(F32, flags=16), "packed"),
-    (W.with_(channels=3), dict(F32, flags=16), "streamed"), (W.with_(channels=7), dict(F32, flags=16), "packed"),
+    (W.with_(channels=3), dict(F32, flags=16), "streamed"), (W.with_(channels=3, nw=64), dict(F32, flags=16), "streamed"),
+    (W.with_(channels=3, q_end=3), dict(F32, flags=16), "streamed"), (W.with_(channels=7), dict(F32, flags=16), "packed"),
+    (MANY.with_(q_end=31, channels=4), dict(F32, flags=16), "streamed"),
+    (MANY.with_(nw=24, q_end=10), dict(F32, flags=16), "streamed"), (MANY.with_(nw=24, q_end=11), dict(F32, flags=16), "packed"),
+    (MANY.with_(nw=64, q_end=31), dict(F32, flags=16), "streamed"),
+    (MANY.with_(nw=64, q_end=20), dict(F32, batch=32, flags=16), "packed"),
+    (MANY.with_(nw=24, nwex=4, q_end=16), dict(F32, flags=16), "streamed"),
+    (MANY.with_(nw=24, lx=5, nq=5, channels=3, q_end=11), dict(F32, flags=16), "packed"),   # three groups
+    (MANY.with_(nw=24, nwex=4, q_end=13), dict(F32, batch=32, flags=16), "packed"),
+    (W, dict(F32, batch=64, flags=16), "packed"),                            # a long pass over little of G
     (W, dict(F32, flags=16 | 64), "packed"), (W, dict(F32, prod=2, flags=16), "packed"),
     (W, dict(F32, flags=32), "packed-deep"), (W.with_(nw=64), dict(F32, flags=8), "mfma-direct"),
     (W.with_(nw=64), dict(F32, flags=24), "packed-mfma-direct")])
