@@ -149,11 +149,12 @@ enum {
                                  (16 bytes per element, each momentum block of Nwg columns padded
                                  to a multiple of 8, with the pass's direct vectors) and the
                                  update kernel copies its operand blocks straight from that
-                                 buffer into LDS (slices of few planes: from G itself, with the
-                                 same sizes and rules); needs an even tile and max_batch * (Ng * ldp
+                                 buffer into LDS; needs an even tile and max_batch * (Ng * ldp
                                  * 16 + direct vectors) more device bytes, ldp = Nc * pcb + 1
-                                 rounded up to 8, pcb = Nwg rounded up to 8.  Combines with
-                                 G4_F_MFMA only (see there). */
+                                 rounded up to 8, pcb = Nwg rounded up to 8.  Slices of few
+                                 planes take the blocks from G itself, under the same rules, and
+                                 need no such buffer (with G4_F_PERSISTENT they pack).  Combines
+                                 with G4_F_MFMA only (see there). */
     G4_F_PACKED_DEEP = 32u,   /* as G4_F_PACKED, with 512-thread blocks and three LDS buffers
                                  (copies run two measurements ahead); one or two K2 rows per
                                  thread, tile = 512/nw or 1024/nw.  Exclusive with the others. */
@@ -315,7 +316,7 @@ int g4_stats(g4_slice *h, g4_stats_t *st);
 /* Override the work tile (K2 rows; 0 keeps it, or takes the variant's default
  * when the variant changes), the pass size (batched mode, at most the
  * allocated max_batch; 0 keeps it) and the kernel variant (G4_VARIANT_*, -1
- * keeps it).  Selecting G4_VARIANT_PACKED allocates its buffer on first use
+ * keeps it).  The packed buffer is allocated when a plan first packs
  * (G4_E_OOM if it does not fit).  G4_E_UNSUPPORTED if the combination cannot
  * run for this slice.  Waits for the handle's stream.
  * Paper: no passage (the paper gives no kernel design for the G_t update; the

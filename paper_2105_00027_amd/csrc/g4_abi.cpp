@@ -110,6 +110,29 @@ bool uses_pack(int variant) {
     return variant == G4_VARIANT_PACKED || variant == G4_VARIANT_PACKED_DEEP || variant == G4_VARIANT_PACKED_MFMA;
 }
 
+// Plane groups of a slice (see build_work)
+int plane_groups(const Plan &P) {
+    int n = 0;
+    const int64_t nwex = P.d.nwex, end = P.d.q_begin + P.d.planes;
+    for (int64_t iQ = P.d.q_begin; iQ < end; ++n) iQ = std::min({end, (iQ / nwex + 1) * nwex, iQ + P.mgroup});
+    return n;
+}
+
+// A packed plan whose slice has too few planes to repay the packing of G: the
+// streamed kernel takes the operands from G itself.
+bool streams(const Plan &P, uint32_t channels) {
+    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent &&
+           stream_packed((int)channels, P.ept, P.mgroup, P.tile, P.d, P.batch, plane_groups(P)) &&
+           stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n,
+                       P.batch);
+}
+
+// Bytes of the packed buffer that a plan needs, for passes of max_batch: none
+// where it streams.
+uint64_t pack_need(const Plan &P, const g4_config &c) {
+    return uses_pack(P.variant) && !streams(P, c.channels) ? (uint64_t)c.max_batch * P.pack_stride : 0;
+}
+
 // Transfer planes per work tile: 8 when Nwex allows, else 4, else 1.
 // G4_PLANE_GROUP=1|4|8 in the environment sets it instead, for measurements
 // (a group larger than Nwex is always partial; the packed MFMA plans, which
@@ -296,7 +319,7 @@ int validate(const g4_config *c, Plan *p) {
         if (P.pack_stride >= (1ull << 31))
             return fail(G4_E_UNSUPPORTED, "packed operands: %llu bytes per measurement above 2^31",
                         (unsigned long long)P.pack_stride);
-        P.pack_bytes = (uint64_t)P.batch * P.pack_stride;
+        P.pack_bytes = pack_need(P, *c);
     }
 
     // --- device memory
@@ -341,23 +364,6 @@ void build_planes(const Plan &P, int nwex, std::vector<int2> &plane_qm) {
         const int64_t iQ = P.d.q_begin + p;
         plane_qm[p] = int2{P.qlist[(size_t)(iQ / nwex)], (int)(iQ % nwex)};
     }
-}
-
-// Plane groups of a slice (see build_work)
-int plane_groups(const Plan &P) {
-    int n = 0;
-    const int64_t nwex = P.d.nwex, end = P.d.q_begin + P.d.planes;
-    for (int64_t iQ = P.d.q_begin; iQ < end; ++n) iQ = std::min({end, (iQ / nwex + 1) * nwex, iQ + P.mgroup});
-    return n;
-}
-
-// A packed plan whose slice has too few planes to repay the packing of G: the
-// streamed kernel takes the operands from G itself.
-bool streams(const Plan &P, uint32_t channels) {
-    return P.variant == G4_VARIANT_PACKED && !P.split && !P.persistent &&
-           stream_packed((int)channels, P.ept, P.mgroup, P.tile, P.d, P.batch, plane_groups(P)) &&
-           stream_runs(P.kind, (int)channels, P.ept, P.mgroup, P.tile, P.d, (int64_t)P.batch * P.d.planes * P.d.n,
-                       P.batch);
 }
 
 // The variant of launch_update that a pass of nb measurements runs: the plan's,
@@ -1656,14 +1662,15 @@ int g4_set_plan(g4_slice *h, int32_t tile, int32_t batch, int32_t variant) {
     // the workspaces were sized for max_batch; only the pass size changes
     G4_HIP(h, hipSetDevice(h->device));
     G4_HIP(h, hipStreamSynchronize(h->stream));
+    P.batch = batch ? batch : h->P.batch;
+    P.pack_bytes = pack_need(P, c);
     rc = ensure_pack(h, P);
     if (rc) return rc;
-    const int keep_batch = h->P.batch;
     h->P.ept = P.ept;
     h->P.tile = P.tile;
     h->P.variant = P.variant;
     h->P.persistent = P.persistent;
-    h->P.batch = batch ? batch : keep_batch;
+    h->P.batch = P.batch;
     h->cfg.tile = c.tile;
     h->cfg.flags = c.flags;
     rc = rebuild_work(h);
@@ -1808,6 +1815,8 @@ int install_plan(g4_slice *h, const g4_config &base, const std::vector<int32_t> 
     int rc = validate(&cc, &P);
     if (rc) return rc;
     if (P.variant != variant) return fail(G4_E_UNSUPPORTED, "variant %d cannot run this slice", variant);
+    P.batch = batch;
+    P.pack_bytes = pack_need(P, cc);
     rc = ensure_pack(h, P);
     if (rc) return rc;
     h->P.ept = P.ept;

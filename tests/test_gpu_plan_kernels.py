@@ -85,3 +85,31 @@ def test_autotuner_times_the_streamed_kernel_once(capfd, monkeypatch):
     deep = sum(1 for e in (1, 2) if e * 32 < 16 + 32)
     assert found["candidates"] == valu + deep
     assert (names[-1], found["variant"]) in (("streamed", 0), ("registers", 0), ("packed-deep", 3))
+
+
+def test_packed_buffer_comes_with_the_plan_that_packs(capfd, monkeypatch):
+    """A streaming packed slice allocates its packed buffer when set_plan installs
+    a plan that packs: another variant, or one whose passes or tiles pack."""
+    import numpy as np
+    from gpu_common import run_slice
+    g4 = g4mod()
+    w = MANY.with_(nw=24, q_end=10)
+    gu, gd, s = host_inputs(w, 6)
+    du, dd = to_dev(gu, 1), to_dev(gd, 1)
+    cfg = config_for(w, **dict(F32, flags=g4.G4_F_PACKED))
+    want, _ = run_slice(config_for(w, **dict(F32, flags=0)), du, dd, s)
+    out = []
+
+    def change(h):
+        g4.g4_accumulate(h, du, dd, s)
+        out.append(g4.g4_readback(h, 1))
+        for batch, variant in ((4, g4.G4_VARIANT_PACKED_DEEP), (2, g4.G4_VARIANT_PACKED), (4, g4.G4_VARIANT_PACKED)):
+            g4.g4_set_plan(h, 0, batch, variant)
+            g4.g4_reset(h)
+            g4.g4_accumulate(h, du, dd, s)
+            out.append(g4.g4_readback(h, 1))
+
+    # passes of two over these plane groups pack
+    assert kernels(capfd, monkeypatch, cfg, change) == ["streamed", "packed-deep", "packed", "streamed"]
+    for o in out:
+        assert np.linalg.norm(o.reshape(want[1].shape) - want[1]) <= 1e-6 * np.linalg.norm(want[1])
