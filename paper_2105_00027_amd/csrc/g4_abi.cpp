@@ -382,9 +382,30 @@ const char *kernel_name(int variant) {
     return variant >= 0 && variant <= kVariantStreamed ? names[variant] : "?";
 }
 
-// PP singlet and triplet, batched: rows K2 and Q - K2 are summed once (kTileMirror)
-bool pair_rows_once(const Plan &P, uint32_t channels) {
+// work tiles of a list that leaves none out
+int64_t whole_tiles(const Plan &P) {
+    return (int64_t)plane_groups(P) * P.d.nc * P.d.nc * ((P.d.nw + P.tile - 1) / P.tile);
+}
+
+double pair_bytes(const Plan &P) { return 2.0 * P.d.ng * P.d.ng * (P.kind == 2 ? 8 : 16); }   // both spins' matrices
+
+// PP singlet and triplet, batched: rows K2 and Q - K2 may be summed once (kTileMirror)
+bool takes_pair_rows(const Plan &P, uint32_t channels) {
     return P.kind != 0 && (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) != 0;
+}
+
+// ... and are where the sums saved outweigh the partner row's read and write of the
+// accumulators, which nothing overlaps.  Time of whole tiles over this, median (5%
+// lowest, 5% highest), on 4901 random shapes:
+//   matrices beyond an XCD's L2, 8 measurements, single planes, 42 frequencies or
+//     78 MB of matrices on: 1.31 (0.97, 2.1); below those lines 0.98 (0.80, 1.23)
+//   smaller matrices, over 10 measurements and two tiles a CU: 1.17 (0.88, 1.74);
+//     fewer measurements or tiles 0.99 (0.79, 1.07)
+bool pair_rows_once(const Plan &P, uint32_t channels) {
+    if (!takes_pair_rows(P, channels)) return false;
+    const Dims &d = P.d;
+    if (pair_bytes(P) > 4e6) return P.batch >= 8 || P.mgroup == 1 || d.nw >= 42 || pair_bytes(P) > 78e6;
+    return P.batch > 10 && whole_tiles(P) > 570;
 }
 
 // The tile order of a plan (see build_work): runs of constant k1 + q for packed
@@ -404,7 +425,7 @@ int default_order(const Plan &P, uint32_t channels) {
     const Dims &d = P.d;
     const bool streamed = streams(P, channels);
     if (uses_pack(P.variant) && !streamed) return d.planes < 32 ? 4 : 3;
-    const double pair = 2.0 * d.ng * d.ng * (P.kind == 2 ? 8 : 16);   // bytes of both spins' matrices
+    const double pair = pair_bytes(P);
     if (plane_groups(P) == 1) return pair > 4e6 ? 4 : 2;
     const bool ph = channels == G4_PH_MAGNETIC || channels == G4_PH_CHARGE ||
                     (streamed && channels == (G4_PH_MAGNETIC | G4_PH_CHARGE));
@@ -459,9 +480,9 @@ void mirror_pairs(const Plan &P, const std::vector<int4> &groups, std::vector<in
     items.resize(kept);
 }
 
-void build_work(const Plan &P, int nwex, int order, uint32_t channels, std::vector<int4> &groups,
+void build_work(const Plan &P, int nwex, int order, uint32_t channels, bool pair, std::vector<int4> &groups,
                 std::vector<int4> &items) {
-    const bool pp = (channels & G4_PP_UPDOWN) != 0, pair = pair_rows_once(P, channels);
+    const bool pp = (channels & G4_PP_UPDOWN) != 0;
     groups.clear();
     items.clear();
     const Dims &d = P.d;
@@ -849,7 +870,7 @@ int rebuild_work(g4_slice *h) {
     }
     std::vector<int4> groups, items;
     const int order = h->order >= 0 ? h->order : default_order(h->P, h->cfg.channels);
-    build_work(h->P, h->cfg.nwex, order, h->cfg.channels, groups, items);
+    build_work(h->P, h->cfg.nwex, order, h->cfg.channels, pair_rows_once(h->P, h->cfg.channels), groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     if (items.size() > h->items_cap) {
         G4_HIP(h, hipStreamSynchronize(h->stream));
@@ -1228,13 +1249,22 @@ int noalloc_accumulate(const g4_config *cfg, void *const acc[3], const void *G_u
     build_planes(P, cfg->nwex, pq);
     std::vector<int32_t> qpos(P.d.nc, -1);
     for (size_t i = 0; i < P.qlist.size(); ++i) qpos[(size_t)P.qlist[i]] = (int32_t)i;
-    std::vector<int4> groups, items;
-    build_work(P, cfg->nwex, default_order(P, cfg->channels), cfg->channels, groups, items);
-    if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     // workspace layout, 256-byte aligned parts
     auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };
     const uint64_t el = P.prec == 0 ? 16 : 8;
     const int64_t pn = (int64_t)P.d.planes * P.d.n;
+    // A batched pass has at most this call's measurements.  A workspace too small for
+    // the list of whole tiles gets the shorter one of rows summed once.
+    Plan call = P;
+    if (P.kind != 0) call.batch = std::min(P.batch, batch);
+    const uint64_t whole = up(kadd.size() * 4) + up(ksub.size() * 4) + up(pq.size() * sizeof(int2)) +
+                           up(qpos.size() * 4) + up(plane_groups(P) * sizeof(int4)) +
+                           up(whole_tiles(P) * sizeof(int4)) + 2 * up((uint64_t)P.nslots * P.batch * pn * el) +
+                           up((uint64_t)P.batch * sizeof(double));
+    const bool pair = pair_rows_once(call, cfg->channels) || (takes_pair_rows(P, cfg->channels) && whole > ws_bytes);
+    std::vector<int4> groups, items;
+    build_work(P, cfg->nwex, default_order(call, cfg->channels), cfg->channels, pair, groups, items);
+    if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     if (P.kind == 0) {
         // The plain kernel adds a launch's measurements one after another to the
         // entry it holds in registers, the same operations in the same order as

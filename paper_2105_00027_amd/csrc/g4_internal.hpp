@@ -79,9 +79,10 @@ __host__ __device__ constexpr int direct_recipes(int channels) {
 // of the tile), and the second's sum only what has no partner in the frequency
 // window (kTileEdge); a momentum that is its own partner keeps whole tiles.
 // 3x3, 50 frequencies, FP64, both channels: 941 -> 597 us per pass of 32
-// (501 with the tiles in their own order).  One
-// measurement a pass keeps whole tiles: there the accumulators bound it, and the
-// partner's would not be loaded ahead (4x4, both channels: 3.34 against 4.46 ms).
+// (501 with the tiles in their own order).  Short
+// passes of small matrices keep whole tiles: there the accumulators bound them, and
+// the partner's would not be loaded ahead (4x4, both channels, one measurement:
+// 3.34 against 4.46 ms).
 constexpr int kTileMirror = 1 << 28, kTileEdge = 1 << 29;
 
 // Arguments of the slice-update kernel.  G elements are complex of the

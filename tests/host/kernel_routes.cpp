@@ -30,7 +30,7 @@ int main() {
         if (validate(&c, &P) != G4_OK) continue;
         std::vector<int4> groups, items;
         if ((int64_t)P.d.planes * P.d.nc * P.d.nc > 200000) continue;
-        build_work(P, c.nwex, 2, c.channels, groups, items);
+        build_work(P, c.nwex, 2, c.channels, false, groups, items);
         for (int nb : {1, P.batch}) {
             const int64_t slot = (int64_t)P.batch * P.d.planes * P.d.n;
             const int v = pass_variant(P, c.channels, (int)groups.size(), (int)items.size(), nb, slot);

@@ -63,7 +63,7 @@ void best_us(const Plan &P, int nwex, uint32_t ch, double *t2, double *t4) {
             double &best = order == 2 ? *t2 : *t4;
             std::vector<int4> groups, items;
             const auto t = std::chrono::steady_clock::now();
-            build_work(P, nwex, order, ch, groups, items);
+            build_work(P, nwex, order, ch, false, groups, items);
             best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t).count());
         }
 }
@@ -88,7 +88,7 @@ int main() {
             return 2;
         }
         std::vector<int4> groups, items;
-        build_work(P, s.nwex, 4, s.channels, groups, items);
+        build_work(P, s.nwex, 4, s.channels, false, groups, items);
         const std::vector<int4> want = orbits(P, groups, (s.channels & G4_PP_UPDOWN) != 0);
         const bool same = items.size() == want.size() && !std::memcmp(items.data(), want.data(), want.size() * sizeof(int4));
         double t2, t4;
@@ -118,7 +118,7 @@ int main() {
         Plan P;
         const int got = validate(&c, &P) == G4_OK ? default_order(P, c.channels) : -1;
         std::vector<int4> groups, items;
-        if (got >= 0) build_work(P, c.nwex, got, c.channels, groups, items);
+        if (got >= 0) build_work(P, c.nwex, got, c.channels, false, groups, items);
         if (got != o.want || plane_groups(P) != (int)groups.size()) {
             std::printf("%dx%d nw %d planes %lld channels %u: order %d, not %d\n", o.l, o.l, o.nw, (long long)(o.q1 - o.q0),
                         o.channels, got, o.want);
