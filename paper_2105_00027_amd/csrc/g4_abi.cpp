@@ -395,17 +395,20 @@ bool takes_pair_rows(const Plan &P, uint32_t channels) {
 }
 
 // ... and are where the sums saved outweigh the partner row's read and write of the
-// accumulators, which nothing overlaps.  Time of whole tiles over this, median (5%
-// lowest, 5% highest), on 4901 random shapes:
-//   matrices beyond an XCD's L2, 8 measurements, single planes, 42 frequencies or
-//     78 MB of matrices on: 1.31 (0.97, 2.1); below those lines 0.98 (0.80, 1.23)
-//   smaller matrices, over 10 measurements and two tiles a CU: 1.17 (0.88, 1.74);
-//     fewer measurements or tiles 0.99 (0.79, 1.07)
+// accumulators, which nothing overlaps: single planes, and longer passes over more
+// frequencies.  Time of whole tiles over this, median (5% lowest, 5% highest), on
+// 4544 random shapes:
+//   matrices beyond an XCD's L2: taken 1.38 (0.98, 2.11), left 0.99 (0.78, 1.30)
+//   smaller ones, which need two tiles a CU besides: 1.22 (0.97, 1.79), left 0.96
+//     (0.76, 1.07)
 bool pair_rows_once(const Plan &P, uint32_t channels) {
     if (!takes_pair_rows(P, channels)) return false;
-    const Dims &d = P.d;
-    if (pair_bytes(P) > 4e6) return P.batch >= 8 || P.mgroup == 1 || d.nw >= 42 || pair_bytes(P) > 78e6;
-    return P.batch > 10 && whole_tiles(P) > 570;
+    const int nw = P.d.nw;
+    const double pair = pair_bytes(P);
+    const bool single = P.mgroup == 1 || P.d.planes == 1;
+    if (pair <= 4e6) return whole_tiles(P) > 512 && (single || (nw >= 28 && P.batch > 10));
+    if (single) return true;
+    return nw >= 42 ? P.batch >= 4 || pair > 26e6 : nw >= 28 ? P.batch >= 8 || pair > 78e6 : P.batch >= 8 && P.mgroup < 8;
 }
 
 // The tile order of a plan (see build_work): runs of constant k1 + q for packed
@@ -689,6 +692,7 @@ struct g4_slice {
     int2 *plane_qm = nullptr;
     int32_t *qpos = nullptr;
     int ngroups = 0, nitems = 0;
+    bool pair_rows = false;   // the tile list sums rows once (kTileMirror)
     size_t items_cap = 0;
     int order = -1;         // tile order (see build_work), -1 = by variant; G4_TILE_ORDER overrides
     void *dir = nullptr;
@@ -870,7 +874,8 @@ int rebuild_work(g4_slice *h) {
     }
     std::vector<int4> groups, items;
     const int order = h->order >= 0 ? h->order : default_order(h->P, h->cfg.channels);
-    build_work(h->P, h->cfg.nwex, order, h->cfg.channels, pair_rows_once(h->P, h->cfg.channels), groups, items);
+    const bool pair = pair_rows_once(h->P, h->cfg.channels);
+    build_work(h->P, h->cfg.nwex, order, h->cfg.channels, pair, groups, items);
     if (items.size() > (size_t)INT32_MAX) return fail(G4_E_UNSUPPORTED, "more than 2^31 work tiles");
     if (items.size() > h->items_cap) {
         G4_HIP(h, hipStreamSynchronize(h->stream));
@@ -885,6 +890,7 @@ int rebuild_work(g4_slice *h) {
     G4_HIP(h, hipStreamSynchronize(h->stream));
     h->ngroups = (int)groups.size();
     h->nitems = (int)items.size();
+    h->pair_rows = pair;
     return G4_OK;
 }
 
@@ -922,6 +928,7 @@ int enqueue_update(g4_slice *h, const GatherArgs &ga, const double *ds, bool tim
     ua.acc[2] = h->acc[2];
     ua.acc_kind = h->cfg.acc;
     ua.tile = P.tile;
+    ua.pair_rows = h->pair_rows;
     ua.persistent = P.persistent;
     ua.d = P.d;
     ua.t = ga.t;
@@ -1361,6 +1368,7 @@ int noalloc_accumulate(const g4_config *cfg, void *const acc[3], const void *G_u
         ua.acc[2] = acc[2];
         ua.acc_kind = cfg->acc;
         ua.tile = P.tile;
+        ua.pair_rows = pair;
         ua.persistent = P.persistent;
         ua.d = P.d;
         ua.t = t;

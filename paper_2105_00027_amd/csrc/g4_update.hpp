@@ -206,7 +206,7 @@ template <typename V, typename CI, int NSG, int NVB, bool MIRROR = false>
 struct Tile {
     int nw, nwg, nc, n, planes, ng;
     int q, m_lo, M, p0, k1, k2, c0, T2;
-    int mode, k2m;      // MIRROR (batched PP singlet / triplet): kTileMirror, kTileEdge; the momentum Q - K2
+    int mode, k2m;      // MIRROR (PP singlet / triplet, rows summed once): kTileMirror, kTileEdge; the momentum Q - K2
     int yr, yc, zr, zc, nY, nZ, nX, nW, nU, nG, nA, nB, nV;
     int rowY, colY, rowZ, colZ, rowX, colX;
     V *Gp, *Vt;
@@ -394,15 +394,19 @@ struct Tile {
 //
 // VALU kernel: thread (r0 = tid / nw, i1 = tid % nw) owns rows
 // r0 + j*RP (j < EPT, RP = 256/nw) of column i1 for every plane of the group.
-template <int KIND, int EPT, int MG, int CH>
+// MIRROR: a list of rows summed once (kTileMirror); a kernel of its own, whose
+// second set of accumulator addresses is in registers all along: whole tiles in it
+// (2x2, 32 frequencies, 35 measurements, FP64, singlet) 262 us, without 199.
+template <int KIND, int EPT, int MG, int CH, bool MIRROR = false>
 __global__ __launch_bounds__(NT, KindInfo<KIND>::waves) void update_kernel(UpdateArgs a) {
     using R = typename KindInfo<KIND>::R;
     using V = typename Cx<R>::V;
     using CI = ChanInfo<CH>;
     constexpr bool PF = KindInfo<KIND>::prefetch;
+    static_assert(!MIRROR || (CI::pair && !PF));
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int tid = threadIdx.x;
-    Tile<V, CI, KindInfo<KIND>::nsg, 1, CI::pair && !PF> t;
+    Tile<V, CI, KindInfo<KIND>::nsg, 1, MIRROR> t;
     t.init(a, a.tile, smem_raw, tid);
     const int nw = t.nw, T2 = t.T2, M = t.M;
     const int RP = NT / nw;            // K2 rows covered by one pass of the block
@@ -578,7 +582,7 @@ __global__ __launch_bounds__(NT, KindInfo<KIND>::waves) void update_kernel(Updat
                 if (CI::tr) acc_update(a.acc[2], a.acc_kind, e, acc[CI::slot_tr][j][m]);
                 if (CI::ps) acc_update(a.acc[0], a.acc_kind, e, acc[0][j][m]);
                 if (CI::pt) acc_update(a.acc[1], a.acc_kind, e, acc[CI::slot_pt][j][m]);
-                if (CI::pair && t.mirrors(m, r0 + j * RP)) {
+                if (MIRROR && t.mirrors(m, r0 + j * RP)) {
                     const int64_t e2 = t.mirror_entry(m, r0 + j * RP, i1);
                     if (CI::ps) acc_update(a.acc[0], a.acc_kind, e2, acc[0][j][m]);
                     if (CI::pt) acc_update(a.acc[1], a.acc_kind, e2, V{-acc[CI::slot_pt][j][m].x, -acc[CI::slot_pt][j][m].y});
@@ -714,13 +718,19 @@ __global__ __launch_bounds__(NT) void update_mfma_kernel(UpdateArgs a) {
 template <int KIND, int EPT, int MG>
 hipError_t launch_ch(int channels, int nitems, size_t lds, const UpdateArgs &a, hipStream_t s) {
     const void *fn = nullptr;
-    switch (channels) {
+    switch (channels | (KIND != 0 && a.pair_rows ? kTileMirror : 0)) {
 #define G4_CASE(CHV)                                                                 \
     case CHV:                                                                        \
         fn = reinterpret_cast<const void *>(&update_kernel<KIND, EPT, MG, CHV>);     \
         break;
         G4_CASE(1) G4_CASE(2) G4_CASE(3) G4_CASE(4) G4_CASE(5) G4_CASE(6) G4_CASE(7)
         G4_CASE(8) G4_CASE(16) G4_CASE(24) G4_CASE(32) G4_CASE(40) G4_CASE(48) G4_CASE(56)
+        G4_CASE(64) G4_CASE(128) G4_CASE(192)
+#undef G4_CASE
+#define G4_CASE(CHV)                                                                    \
+    case CHV | kTileMirror:                                                             \
+        fn = reinterpret_cast<const void *>(&update_kernel<KIND, EPT, MG, CHV, KIND != 0>); \
+        break;
         G4_CASE(64) G4_CASE(128) G4_CASE(192)
 #undef G4_CASE
         default:

@@ -45,10 +45,14 @@ int main() {
     // few measurements of few frequencies, and small matrices of few measurements or tiles, keep whole tiles
     struct Case { int lx, ly, nw, nwex, nq; int64_t q0, q1; int prod, batch; uint32_t ch; int want; };
     const Case cases[] = {{4, 4, 32, 8, 16, 0, 16, 0, 2, 192, 0},  {4, 4, 32, 8, 16, 0, 16, 0, 8, 192, 1},
-                          {8, 8, 16, 8, 64, 0, 16, 1, 4, 64, 0},   {8, 8, 16, 1, 64, 0, 16, 1, 2, 64, 1},
-                          {4, 4, 64, 8, 16, 0, 16, 1, 1, 128, 1},  {2, 2, 32, 8, 4, 0, 32, 0, 32, 192, 0},
-                          {3, 2, 24, 5, 6, 3, 27, 0, 12, 192, 1},  {3, 2, 24, 5, 6, 3, 27, 0, 4, 192, 0},
-                          {3, 2, 24, 5, 6, 3, 27, 1, 1, 192, 0},   {4, 4, 64, 8, 16, 0, 128, 1, 64, 7, 0}};
+                          {8, 8, 16, 8, 64, 0, 16, 1, 8, 64, 0},   {8, 8, 16, 4, 64, 0, 16, 1, 8, 64, 1},
+                          {8, 8, 16, 1, 64, 0, 16, 1, 2, 64, 1},   {2, 2, 32, 8, 4, 0, 32, 0, 32, 192, 0},
+                          {4, 4, 64, 8, 16, 0, 16, 1, 3, 128, 0},  {4, 4, 64, 8, 16, 0, 16, 1, 4, 128, 1},
+                          {4, 4, 64, 8, 16, 0, 16, 0, 1, 128, 1},  {3, 2, 34, 5, 6, 3, 27, 0, 12, 192, 1},
+                          {3, 2, 34, 5, 6, 3, 27, 1, 12, 192, 1},  {3, 2, 34, 5, 6, 3, 27, 0, 10, 192, 0},
+                          {3, 2, 46, 3, 6, 2, 18, 1, 12, 192, 1},  {3, 2, 46, 3, 6, 2, 18, 0, 3, 192, 0},
+                          {3, 2, 70, 1, 6, 0, 6, 0, 3, 192, 1},    {8, 8, 8, 12, 64, 348, 349, 1, 4, 192, 1},
+                             {3, 2, 70, 1, 6, 0, 6, 1, 3, 192, 1},  {4, 4, 64, 8, 16, 0, 128, 1, 64, 7, 0}};
     g4_config c;
     Plan P;
     for (const Case &k : cases) {

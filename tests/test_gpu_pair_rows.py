@@ -14,9 +14,9 @@ from synth import Workload
 pytestmark = pytest.mark.gpu
 
 PAIR = ref.PP_SINGLET | ref.PP_TRIPLET
-G8 = Workload("3x2, groups of 8", lx=3, ly=2, nw=24, nwex=5, nq=6, q_list=(4, 0, 5, 1, 3, 2), q_begin=3, q_end=27,
+G8 = Workload("3x2, groups of 8", lx=3, ly=2, nw=34, nwex=5, nq=6, q_list=(4, 0, 5, 1, 3, 2), q_begin=3, q_end=27,
               seed=51, wid=51, channels=PAIR)
-G4 = G8.with_(name="3x2, groups of 4", nwex=3, nq=6, q_begin=2, q_end=18, nw=34)
+G4 = G8.with_(name="3x2, groups of 4", nwex=3, nq=6, q_begin=2, q_end=18, nw=46)
 G1 = G8.with_(name="3x2, single planes", nwex=1, nq=6, q_begin=0, q_end=6, nw=70)
 _cache = {}
 
