@@ -125,5 +125,17 @@ int main() {
             ++bad;
         }
     }
+    // a call of few measurements makes the quicker list
+    g4_config c;
+    g4_config_init(&c);
+    c.lx = c.ly = 8; c.nw = 22; c.nq = 1; c.q_end = 1; c.channels = 1; c.max_batch = 16;
+    for (int mode : {G4_MODE_PLAIN, G4_MODE_BATCHED}) {
+        c.mode = mode;
+        Plan P;
+        if (validate(&c, &P) != G4_OK || call_order(P, 1, 7) != 2 || call_order(P, 1, 8) != 4) {
+            std::printf("one plane of 8x8, mode %d: orders %d and %d\n", mode, call_order(P, 1, 7), call_order(P, 1, 8));
+            ++bad;
+        }
+    }
     return bad ? 1 : 0;
 }
