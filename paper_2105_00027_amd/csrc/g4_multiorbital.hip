@@ -57,6 +57,7 @@ struct MoArgs {
     int64_t total;               // entries of this launch
     int64_t side;                // N nb^2
     int lx, ly, nw, nwg, nb, ngb, channel, batch, planes;
+    int matrix;                  // mo_mfma_kernel runs (mo_uses_mfma)
     int2 qm[kMoPlanes];          // (q, m) per plane of the launch
     double sign[kMoLong];
 };
@@ -744,9 +745,15 @@ bool mo_uses_two(const MoArgs &a) {
 
 // Four orbitals in FP32 fill the 16 x 16 matrix instruction (three use 81 of its
 // 256 products and stay on the vector units); the kernel takes 32-bit byte
-// offsets within four matrices.
-bool mo_uses_mfma(int nb, bool f32, int64_t g_stride) {
-    return f32 && nb == 4 && g_stride * 8 < ((int64_t)1 << 30);
+// offsets within four matrices.  Each of its steps takes four measurements, and a
+// block all of a plane pair's orbitals of 16 momentum-frequency pairs: calls of
+// fewer measurements, and few blocks of few measurements, are quicker on the rows
+// kernel (2561 random shapes, its time over this kernel's, median, 5% lowest and
+// highest: taken here 1.39 (0.98, 2.29), left 0.97 (0.78, 1.12)).  `batch` counts the whole call's: what
+// a launch may hold follows from the choice, made once for all of a call.
+bool mo_uses_mfma(const MoArgs &a, bool f32, int batch) {
+    if (!f32 || a.nb != 4 || a.g_stride * 8 >= ((int64_t)1 << 30) || batch < 4) return false;
+    return a.planes == 1 || mo_mfma_blocks(a, 2) > 128 || batch > 40;
 }
 
 template <typename R>
@@ -757,7 +764,7 @@ hipError_t launch_mo(const MoArgs &a, hipStream_t st) {
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
     const dim3 g((unsigned)blocks), b(256);
     if constexpr (std::is_same<R, float>::value)
-        if (mo_uses_mfma(a.nb, true, a.g_stride)) {
+        if (a.matrix) {
             const int tq = a.planes > 1 ? 2 : 1;
             const int64_t mb = mo_mfma_blocks(a, tq);
             if (mb >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
@@ -849,10 +856,10 @@ extern "C" int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex
         for (int64_t p0 = 0; p0 < planes; p0 += kMoPlanes) {
             const int np = (int)std::min<int64_t>(kMoPlanes, planes - p0);
             MoArgs shape{};
-            shape.nb = nb; shape.planes = np; shape.side = side;
+            shape.nb = nb; shape.planes = np; shape.side = side; shape.g_stride = ngb * ngb;
             shape.channel = both ? CH_MAG | CH_CHG : 1 << c;
-            const int most = mo_uses_mfma(nb, prod == G4_PROD_F32, ngb * ngb) || (prod == G4_PROD_F64 && mo_uses_two(shape))
-                                 ? kMoLong : kMoBatch;
+            const bool matrix = mo_uses_mfma(shape, prod == G4_PROD_F32, batch);
+            const int most = matrix || (prod == G4_PROD_F64 && mo_uses_two(shape)) ? kMoLong : kMoBatch;
             for (int b0 = 0; b0 < batch; b0 += most) {
                 MoArgs a{};
                 a.g_stride = ngb * ngb;
@@ -867,6 +874,7 @@ extern "C" int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex
                 a.channel = both ? CH_MAG | CH_CHG : 1 << c;
                 a.batch = std::min(most, batch - b0);
                 a.planes = np;
+                a.matrix = matrix;
                 for (int i = 0; i < np; ++i) {
                     const int64_t iQ = q_begin + p0 + i;
                     a.qm[i] = int2{ql[(size_t)(iQ / nwex)], (int)(iQ % nwex)};

@@ -130,6 +130,15 @@ def test_four_orbital_matrix_kernel(lx, ly, nw, nwex, q0, q1, count):
         assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want), c
 
 
+# Sizes at which calls of few measurements run the matrix kernel, and either side of them: single planes, blocks beyond
+# 128 with K and planes that do not fill their fours and pairs, three and four measurements, 40 and 41.
+@pytest.mark.parametrize("lx,ly,nw,nwex,q0,q1,count", [(2, 1, 10, 2, 1, 2, 4), (2, 1, 10, 2, 1, 2, 3), (3, 1, 6, 3, 2, 3, 9),
+                                                       (3, 1, 14, 3, 1, 4, 5), (3, 1, 14, 3, 0, 3, 3), (3, 1, 14, 1, 0, 2, 6),
+                                                       (1, 1, 6, 4, 0, 3, 40), (1, 1, 6, 4, 0, 3, 41)])
+def test_four_orbital_kernel_choice(lx, ly, nw, nwex, q0, q1, count):
+    test_four_orbital_matrix_kernel(lx, ly, nw, nwex, q0, q1, count)
+
+
 # The two-orbital PH kernel: each channel set, batches around its launches (32 in FP32, 128 in FP64), an accumulator that
 # is not zero, columns that do not fill a block.
 @pytest.mark.parametrize("channels", [1, 2, 3, 7])
@@ -149,11 +158,12 @@ def test_two_orbital_kernel(channels, prod, count):
 # The parts of a long launch (sums of 32 measurements in FP32) join in more than FP32: a call gives what calls of 32
 # give, whose sums meet in the complex128 accumulator.  Each of up to three additions rounds away at most 2^-24 of the
 # sum, kept to 2^-24 of itself: 5 * 2^-48 in all, 2^-53 a call on the other side; the bar is 2^-44 of the largest sum.
-@pytest.mark.parametrize("planes,count", [(3, 131), (1, 128), (2, 64), (2, 33)])
+# The sizes are those where calls of 32 and fewer run the matrix kernel too.
+@pytest.mark.parametrize("planes,count", [(5, 133), (1, 128), (6, 64), (5, 37)])
 def test_four_orbital_parts_keep_their_width(planes, count):
     import torch
     g4 = g4mod()
-    nb, nw = 4, 6
+    nb, nw = 4, 16
     w = Workload("mo4-parts", lx=2, ly=1, nw=nw, nwex=3, nq=2, q_begin=0, q_end=planes)
     print(f"\ncase mo4 parts planes={planes} count={count}", flush=True)
     rng = np.random.default_rng(7 + count)
