@@ -734,13 +734,22 @@ int64_t mo_mfma_blocks(const MoArgs &a, int tq) {
     return ((a.planes + tq - 1) / tq * t4 * t4 + 7) / 8 * 8;
 }
 
-// The blocks of a launch of mo_two_kernel, and whether it runs: both channels of
-// two orbitals in one launch pay at every size, one channel from a block per CU on
-// (2x2, 32 measurements, rows kernel against this one: 60 blocks 28 : 39 us, 96
-// 36 : 45, 256 69 : 54, 512 114 : 79).
+// The blocks of a launch of mo_two_kernel, and whether it runs: one channel of two
+// orbitals from a block per CU on (2x2, 32 measurements, rows kernel against this
+// one: 60 blocks 28 : 39 us, 96 36 : 45, 256 69 : 54, 512 114 : 79), both channels
+// where they share a launch.
 int64_t mo_two_blocks(const MoArgs &a) { return (int64_t)a.planes * (a.side / 8) * ((a.side + 255) / 256); }
 bool mo_uses_two(const MoArgs &a) {
     return a.nb == 2 && a.channel != CH_PP && (a.channel == (CH_MAG | CH_CHG) || mo_two_blocks(a) >= 256);
+}
+
+// Whether the `planes` planes of a call's magnetic and charge slices share launches.
+// Small slices sum their measurements in a chain that two launches of the rows
+// kernel shorten: its time over this kernel's, median (5% lowest, 5% highest) on
+// 1465 random shapes, shared 1.45 (1.17, 3.0), not shared 0.98 (0.84, 1.12).
+bool mo_both(int64_t planes, int64_t side, bool f32, int batch) {
+    const int64_t n = side / 4, rows = planes * n * ((side + 255) / 256);
+    return !(rows <= 284 && n <= 42 && batch > 12 && (f32 || batch <= 40));
 }
 
 // Four orbitals in FP32 fill the 16 x 16 matrix instruction (three use 81 of its
@@ -851,8 +860,9 @@ extern "C" int g4_accumulate_mo(int32_t lx, int32_t ly, int32_t nw, int32_t nwex
     for (int c = 0; c < 3; ++c) {
         if (!acc[c]) continue;
         // two orbitals: magnetic and charge in the same launches
-        const bool both = nb == 2 && c == 0 && acc[1];
-        if (nb == 2 && c == 1 && acc[0]) continue;
+        const bool pair = nb == 2 && c < 2 && acc[0] && acc[1] && mo_both(planes, side, prod == G4_PROD_F32, batch);
+        const bool both = pair && c == 0;
+        if (pair && c == 1) continue;
         for (int64_t p0 = 0; p0 < planes; p0 += kMoPlanes) {
             const int np = (int)std::min<int64_t>(kMoPlanes, planes - p0);
             MoArgs shape{};

@@ -155,6 +155,37 @@ def test_two_orbital_kernel(channels, prod, count):
         check_entries(got[ch], ref.accumulate_mo(w, nb, ch, gu, gd, s), 1e-12 if prod == 0 else 1e-6, what="channel %d" % ch)
 
 
+# Small slices of two orbitals, either side of the lines at which their PH channels share launches (n 42, 284 rows'
+# blocks, 12 and 40 measurements): both channels in one call give what a call each gives, and the oracle's entries.
+@pytest.mark.parametrize("lx,nw,planes,prod,count", [(3, 14, 1, 1, 13), (3, 14, 1, 1, 12), (2, 22, 1, 1, 13), (2, 6, 6, 1, 33),
+                                                     (2, 20, 8, 1, 14), (2, 20, 7, 1, 14), (2, 6, 4, 0, 40), (2, 6, 4, 0, 41)])
+def test_two_orbital_channels_together_and_alone(lx, nw, planes, prod, count):
+    import torch
+    g4 = g4mod()
+    nb = 2
+    w = Workload("mo2-both", lx=lx, ly=1, nw=nw, nwex=4, nq=2, q_begin=0, q_end=planes)
+    print(f"\ncase mo2 both lx={lx} nw={nw} planes={planes} prod={prod} count={count}", flush=True)
+    gu, gd, s = inputs(w, nb, count, 11 * count + planes)
+    dtype = np.complex64 if prod else np.complex128
+    du, dd = (torch.from_numpy(g.astype(dtype)).cuda() for g in (gu, gd))
+    side = w.n * nb * nb
+
+    def call(channels):
+        acc = [torch.zeros((planes, side, side), dtype=torch.complex128, device="cuda") if channels >> c & 1 else None
+               for c in range(2)]
+        g4.g4_accumulate_mo(lx, 1, nw, 4, nb, 2, None, 0, planes, channels, prod, du, dd, s, *acc)
+        return acc
+
+    both, alone = call(3), [call(1)[0], call(2)[1]]
+    idx = np.random.default_rng(1).integers(0, planes * side * side, size=200)
+    gu, gd = (g.astype(dtype).astype(np.complex128) for g in (gu, gd))
+    for c in range(2):
+        want = ref.entries_mo(w, nb, 1 << c, gu, gd, s, idx)
+        for got in (both[c], alone[c]):
+            got = got.cpu().numpy().reshape(-1)[idx]
+            assert np.linalg.norm(got - want) <= (1e-6 if prod else 1e-12) * np.linalg.norm(want), c
+
+
 # The parts of a long launch (sums of 32 measurements in FP32) join in more than FP32: a call gives what calls of 32
 # give, whose sums meet in the complex128 accumulator.  Each of up to three additions rounds away at most 2^-24 of the
 # sum, kept to 2^-24 of itself: 5 * 2^-48 in all, 2^-53 a call on the other side; the bar is 2^-44 of the largest sum.
