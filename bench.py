@@ -59,8 +59,9 @@ MFMA_F64_PEAK = 78.6e12                             # dense FP64 MFMA
 FLOPS_PER_EU = {1: 24, 2: 24, 4: 16}                 # per channel: direct 8 + exchange 16; PP 16
 DIRECT_FLOPS = 8                                     # the PH direct term's share
 VARIANTS = ["valu", "mfma-direct", "packed-lds", "packed-lds-deep", "packed-lds-mfma-direct"]
-KERNELS = ["update_kernel", "update_mfma_kernel", "update_packed_kernel", "update_packed_kernel",
-           "update_packed_mfma_kernel"]
+# a plan of variant 0 or 2 may stream its operands instead (update_stream_kernel); the library's log line says which
+KERNELS = ["update_kernel or update_stream_kernel", "update_mfma_kernel", "update_packed_kernel or update_stream_kernel",
+           "update_packed_kernel", "update_packed_mfma_kernel"]
 REPS = 3
 
 
@@ -377,7 +378,7 @@ class Bench:
         torch.cuda.synchronize()
         ms = [self.timed(call, steps) / steps for _ in range(REPS)]
         med = statistics.median(ms)
-        # by sites (n >= 72 on this lattice) the products are per pair of sites: 1 / Nc of the
+        # by sites (the library's line on this lattice is 72 vertices) the products are per pair of sites: 1 / Nc of the
         # full ones, without the Fourier sums over the lattice
         flops = 8.0 * count * (w.ng * n * n + w.ng * w.ng * n) / (w.lx * w.ly if n >= 72 else 1)
         peak = MFMA_F64_PEAK if c128 else MFMA_F32_PEAK

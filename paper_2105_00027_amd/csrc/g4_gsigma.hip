@@ -569,8 +569,8 @@ bool gsigma_by_sites(const GsShape &s) {
     const uint64_t esize = 2 * sizeof(T), n = (uint64_t)s.n;
     const uint64_t extra = (n * n + (uint64_t)s.nwg * n) * esize + (n + s.nc + 1) * 4 + 64;
     const uint64_t lds = (uint64_t)(2 * s.nc * 64 + s.lx + s.ly) * esize;
-    return s.nc >= 4 && s.n >= 72 && (dft_in_registers(s.lx, s.ly) || s.n >= 4 * s.nc) && s.n <= kSiteVertices && lds <= 140 * 1024 && extra <= (uint64_t)s.ng * n * esize &&
-           (int64_t)s.count * s.nc <= 65535;
+    return s.nc >= 4 && s.n >= 72 && (dft_in_registers(s.lx, s.ly) || s.n >= 4 * s.nc) && s.n <= kSiteVertices &&
+           lds <= 140 * 1024 && extra <= (uint64_t)s.ng * n * esize && (int64_t)s.count * s.nc <= 65535;
 }
 
 template <typename T, bool BH, int TM>

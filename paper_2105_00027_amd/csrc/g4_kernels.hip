@@ -19,16 +19,16 @@ template <typename R> struct Cx;
 template <> struct Cx<double> { using V = double2; };
 template <> struct Cx<float> { using V = float2; };
 
-// ---------------------------------------------------------------------------
-// Direct-term vectors: element (slot, b, p, K) at slot*dir_slot_stride +
-// b*dir_b_stride + p*n + K; slot 0 = magnetic (G_up - G_dn), slot 1 = charge
-// (G_up + G_dn), present when the slot bit is set.
 // weight of measurement b, and the store of all of them by one block
 __device__ __forceinline__ double weight(const GatherArgs &a, int b) { return a.sign_out ? a.sgn[b] : a.sign[b]; }
 __device__ __forceinline__ void store_weights(const GatherArgs &a, bool this_block) {
     if (a.sign_out && this_block && (int)threadIdx.x < a.batch) a.sign_out[threadIdx.x] = a.sgn[threadIdx.x];
 }
 
+// ---------------------------------------------------------------------------
+// Direct-term vectors: element (slot, b, p, K) at slot*dir_slot_stride +
+// b*dir_b_stride + p*n + K; slot 0 = magnetic (G_up - G_dn), slot 1 = charge
+// (G_up + G_dn), present when the slot bit is set.
 template <typename R>
 __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     using V = typename Cx<R>::V;

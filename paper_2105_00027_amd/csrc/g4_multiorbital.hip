@@ -458,6 +458,10 @@ __global__ __launch_bounds__(256) void mo_two_kernel(MoArgs a) {
             }
 }
 
+constexpr int kMoTk = 4;         // K2 of a wave of mo_mfma_kernel
+// its dynamic LDS: the low parts of the sums, only where a launch has more than one part
+size_t mo_mfma_lds(int batch, int tq) { return batch > kMoBatch ? (size_t)256 * kMoTk * tq * 2 * 16 : 0; }
+
 // Four orbitals, FP32: the orbital labels of one (Q, K1, K2) make the exchange
 // (and PP) term a 16 x 16 outer product summed over measurements and spins,
 //   PH  [(b1, b4), (b3, b2)] += G_s(K1+Q b1, K2+Q b4) (-s_b G_s(K2 b3, K1 b2)),
@@ -484,10 +488,6 @@ __global__ __launch_bounds__(256) void mo_two_kernel(MoArgs a) {
 // units (eight launches, 30 TFLOP/s), here 7.1 ms (58 TFLOP/s; 2.7 ms at the rate
 // of a large FP32 product).  What is left is the operands' way from L2: runs of
 // four elements (32 bytes); with the row operand always in L1 5.1 ms.
-constexpr int kMoTk = 4;         // K2 of a wave of mo_mfma_kernel
-// dynamic LDS: the low parts of the sums, only where a launch has more than one part
-size_t mo_mfma_lds(int batch, int tq) { return batch > kMoBatch ? (size_t)256 * kMoTk * tq * 2 * 16 : 0; }
-
 template <int TQ, bool PP>
 __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(256, 2) void mo_mfma_kernel(MoArgs a) {
         for (int t = 0; t < TQ; ++t) re[j][t] = im[j][t] = rs[j][t] = is[j][t] = f4{0.f, 0.f, 0.f, 0.f};
 
     // direct operands: a thread forms one (K of four, plane, orbital pair) of each side; threads past them repeat
-    const int sid = TQ == 4 ? tid : tid % (64 * TQ);
+    const int sid = tid % (64 * TQ);
     const int sk = sid / (TQ * 16), st = (sid / 16) % TQ, se = sid & 15;
     unsigned ao = 0, bo = 0;
     if (!PP) {
