@@ -485,7 +485,7 @@ size_t mo_mfma_lds(int batch, int tq) { return batch > kMoBatch ? (size_t)256 * 
 // The block's four waves are four neighbouring K1; the direct operands of its
 // 4 K1, 4 K2 and TQ planes are formed once in LDS, four measurements at a time.
 // The 2x2 cluster, Nw = 32, 16 planes, 256 measurements: 13.0 ms on the vector
-// units (eight launches, 30 TFLOP/s), here 7.1 ms (58 TFLOP/s; 2.7 ms at the rate
+// units (eight launches, 30 TFLOP/s), here 7.2 ms (57 TFLOP/s; 2.7 ms at the rate
 // of a large FP32 product).  What is left is the operands' way from L2: runs of
 // four elements (32 bytes); with the row operand always in L1 5.1 ms.
 template <int TQ, bool PP>
