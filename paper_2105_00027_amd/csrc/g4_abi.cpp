@@ -432,7 +432,8 @@ int default_order(const Plan &P, uint32_t channels) {
     if (plane_groups(P) == 1) return pair > 4e6 ? 4 : 2;
     const bool ph = channels == G4_PH_MAGNETIC || channels == G4_PH_CHARGE ||
                     (streamed && channels == (G4_PH_MAGNETIC | G4_PH_CHARGE));
-    return ph && P.kind == 2 && d.nc >= 32 && d.planes < 32 && (P.batch >= 32 ? pair > 16e6 : P.batch >= 8 && pair > 32e6) ? 4 : 2;
+    return ph && P.kind == 2 && d.nc >= 32 && d.planes < 32 &&
+           (P.batch >= 32 ? pair > 16e6 : P.batch >= 8 && pair > 32e6) ? 4 : 2;
 }
 
 // The order of a list made for one call of `batch` measurements (g4_accumulate_into).
