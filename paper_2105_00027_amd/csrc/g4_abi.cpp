@@ -416,8 +416,12 @@ bool pair_rows_once(const Plan &P, uint32_t channels) {
 // random shapes, windows over orbits with the streamed kernel, or runs over orbits
 // with the packed one, median, 5% lowest and highest)
 //   packed operands of fewer than 32 planes: 1.01 (0.96, 1.13);
-//   one plane group, whose matrices exceed an XCD's L2: 1.02 (0.98, 1.20), the 8x8
-//     three-channel share 1.6;
+//   one plane group, whose matrices exceed an XCD's L2: plain 1.02 (0.98, 1.10);
+//     batched passes, where tiles of three rows or more are at most 6000 frequencies
+//     times measurements long, or clusters of 16 sites take up to 8 measurements:
+//     1.03 (0.95, 1.21), the 8x8 three-channel share 1.6.  Longer passes drift apart,
+//     and with them the tiles that share a block: 0.99 (0.78, 1.07) on 3686 shapes of
+//     80 to 256 frequencies;
 //   several groups, whose transfers spread an orbit wider than an L2, in long FP32
 //     passes of PH channels on large clusters and matrices: 1.03 (0.91, 1.17), the
 //     6x6 share of 14 planes 1.05.
@@ -429,7 +433,9 @@ int default_order(const Plan &P, uint32_t channels) {
     const bool streamed = streams(P, channels);
     if (uses_pack(P.variant) && !streamed) return d.planes < 32 ? 4 : 3;
     const double pair = pair_bytes(P);
-    if (plane_groups(P) == 1) return pair > 4e6 ? 4 : 2;
+    if (plane_groups(P) == 1)
+        return pair > 4e6 && (P.kind == 0 || (P.tile >= 3 && (int64_t)d.nw * P.batch <= 6000) ||
+                              (P.batch <= 8 && d.nc >= 16)) ? 4 : 2;
     const bool ph = channels == G4_PH_MAGNETIC || channels == G4_PH_CHARGE ||
                     (streamed && channels == (G4_PH_MAGNETIC | G4_PH_CHARGE));
     return ph && P.kind == 2 && d.nc >= 32 && d.planes < 32 &&
