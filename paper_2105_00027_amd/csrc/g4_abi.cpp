@@ -415,30 +415,34 @@ bool pair_rows_once(const Plan &P, uint32_t channels) {
 // operands, windows for register-staged and streamed ones; or orbits (on 6996
 // random shapes, windows over orbits with the streamed kernel, or runs over orbits
 // with the packed one, median, 5% lowest and highest)
-//   packed operands of fewer than 32 planes: 1.01 (0.96, 1.13);
+//   packed operands of fewer than 32 planes: 1.01 (0.96, 1.13), but for several
+//     groups of single planes: 0.99 (0.88, 1.03);
 //   one plane group, whose matrices exceed an XCD's L2: plain 1.02 (0.98, 1.10);
 //     batched passes, where tiles of three rows or more are at most 6000 frequencies
 //     times measurements long, or clusters of 16 sites take up to 8 measurements:
-//     1.03 (0.95, 1.21), the 8x8 three-channel share 1.6.  Longer passes drift apart,
-//     and with them the tiles that share a block: 0.99 (0.78, 1.07) on 3686 shapes of
-//     80 to 256 frequencies;
+//     1.03 (0.95, 1.21), the 8x8 three-channel share 1.6 (not PP of 4 sites: 0.98
+//     (0.66, 1.12)).  In longer passes the tiles that share a block drift apart: 0.99
+//     (0.78, 1.07) on 3686 shapes of 80 to 256 frequencies;
 //   several groups, whose transfers spread an orbit wider than an L2, in long FP32
 //     passes of PH channels on large clusters and matrices: 1.03 (0.91, 1.17), the
 //     6x6 share of 14 planes 1.05.
 // Several groups otherwise lose: 0.99 (0.88, 1.06), three channels of 128
-// frequencies at 6x6 0.70.
+// frequencies at 6x6 0.70, and so do long FP32 passes of groups of single planes:
+// 0.99 (0.63, 1.13).
 int default_order(const Plan &P, uint32_t channels) {
     if (channels & (G4_PP_SINGLET | G4_PP_TRIPLET)) return pair_rows_once(P, channels) && P.mgroup < 8 ? 4 : 2;
     const Dims &d = P.d;
     const bool streamed = streams(P, channels);
-    if (uses_pack(P.variant) && !streamed) return d.planes < 32 ? 4 : 3;
+    const bool singles = P.mgroup == 1 && d.planes > 1;   // several groups of a plane
+    if (uses_pack(P.variant) && !streamed) return d.planes < 32 && !singles ? 4 : 3;
     const double pair = pair_bytes(P);
     if (plane_groups(P) == 1)
-        return pair > 4e6 && (P.kind == 0 || (P.tile >= 3 && (int64_t)d.nw * P.batch <= 6000) ||
-                              (P.batch <= 8 && d.nc >= 16)) ? 4 : 2;
+        return pair > 4e6 && (P.kind == 0 || (P.batch <= 8 && d.nc >= 16) ||
+                              (P.tile >= 3 && (int64_t)d.nw * P.batch <= 6000 &&
+                               !((channels & G4_PP_UPDOWN) && d.nc <= 4))) ? 4 : 2;
     const bool ph = channels == G4_PH_MAGNETIC || channels == G4_PH_CHARGE ||
                     (streamed && channels == (G4_PH_MAGNETIC | G4_PH_CHARGE));
-    return ph && P.kind == 2 && d.nc >= 32 && d.planes < 32 &&
+    return ph && P.kind == 2 && !singles && d.nc >= 32 && d.planes < 32 &&
            (P.batch >= 32 ? pair > 16e6 : P.batch >= 8 && pair > 32e6) ? 4 : 2;
 }
 

@@ -110,7 +110,10 @@ int main() {
                             {4, 64, 8, 16, 0, 31, 1, 1, 64, G4_F_PACKED, 4},  {6, 32, 4, 36, 0, 8, 1, 1, 64, G4_F_PACKED, 4},
                             {6, 64, 8, 5, 13, 27, 24, 1, 16, 0, 2},           {4, 128, 2, 16, 8, 9, 7, 0, 27, 0, 2},
                             {4, 128, 2, 16, 8, 9, 7, 0, 8, 0, 4},             {2, 128, 8, 4, 0, 8, 1, 0, 8, 0, 2},
-                            {4, 64, 8, 16, 0, 8, 1, 0, 64, 0, 4},             {4, 160, 4, 16, 4, 6, 7, 1, 64, 0, 2}};
+                            {4, 64, 8, 16, 0, 8, 1, 0, 64, 0, 4},             {4, 160, 4, 16, 4, 6, 7, 1, 64, 0, 2},
+                            {6, 50, 1, 36, 2, 12, 1, 1, 30, 0, 2},            {6, 50, 1, 36, 2, 3, 1, 1, 30, 0, 4},
+                            {2, 128, 1, 4, 0, 1, 4, 0, 11, 0, 2},             {3, 128, 1, 9, 0, 9, 1, 1, 32, G4_F_PACKED, 3},
+                            {3, 128, 1, 9, 0, 1, 1, 1, 32, G4_F_PACKED, 4}};
     for (const Order &o : orders) {
         g4_config c;
         g4_config_init(&c);
